@@ -12,11 +12,13 @@
 //     gfx950 direct-to-LDS loads (global_load_lds_dwordx4) fill a double
 //     buffer of K = 64 stages: every operand row of a stage is one whole
 //     128-byte line, which the direct-to-LDS path moves at about twice the
-//     rate of half lines.  One barrier per stage.
-//   * Half of the waves issue all the stage loads and the other half all the
+//     rate of half lines.  A stage is loaded in parts, each issued as soon as
+//     the space it takes has been read by every wave (two barriers per stage),
+//     so a load has about a stage and a quarter to land.
+//   * Half of the waves issue all the direct loads and the other half all the
 //     output stores, so no wave's in-order memory counter mixes the two (a
 //     wait for a stage never waits for a tile's worth of stores to drain).
-//   * Each wave reads its LDS fragments one MFMA K step ahead of its MFMAs
+//   * Each wave reads its LDS fragments a quarter of a stage ahead of its MFMAs
 //     (16 x 16 x 32 MFMAs: half the accumulator reads and writes per flop of
 //     the 32 x 32 x 16 form, measured 3-4 % faster on whole calls).
 //   * Calls of many m-tiles run both GEMMs in one persistent kernel with a
@@ -106,47 +108,19 @@ __device__ __forceinline__ const void* uniform_ptr(const void* p) {
 // instruction's immediate offset stays 0 (it would shift the LDS address too).
 // They are inline assembly so that the compiler's wait-count pass does not
 // treat every later LDS read as aliasing them (it would drain all in-flight
-// stages); the kernel waits on them explicitly with wait_loads().  Because the
-// compiler does not see the instruction, it also does not insert the wait
-// states the hardware needs before it: a VALU write of an SGPR (v_readfirstlane
-// of the base) needs 5 wait states before a vector-memory instruction reads it,
-// and an SALU write of M0 needs 1 before an LDS DMA; the s_nop 4 inside each
-// statement provides 5.
-//
-// Direct load of row block I: byte offset lane_off + I * blk_bytes, formed
-// inside the statement (v_mad_u32_u24; both factors stay below 2^24) so the
-// compiler keeps no per-block offset registers alive across the K loop.
-template <int I>
-__device__ __forceinline__ void lds_dma16_blk(const void* base, uint32_t lane_off, uint32_t blk_bytes,
-                                              uint32_t lds_addr) {
-    uint32_t off;
-    asm volatile("v_mad_u32_u24 %0, %1, %2, %3\n\ts_nop 4\n\tglobal_load_lds_dwordx4 %0, %4"
-                 : "=&v"(off)
-                 : "n"(I), "s"(blk_bytes), "v"(lane_off), "s"(uniform_ptr(base)),
-                   "{m0}"(__builtin_amdgcn_readfirstlane(lds_addr))
-                 : "memory");
-}
-
-// Direct load of rows first + ld_row, clamped to last (rows past an expert's
-// end repeat its last row): offset min(first + ld_row, last) * pitch + col_b.
-__device__ __forceinline__ void lds_dma16_clamped(const void* base, uint32_t ld_row, int first, int last,
-                                                  uint32_t pitch, uint32_t col_b, uint32_t lds_addr) {
-    uint32_t off;
-    asm volatile("v_add_u32 %0, %1, %2\n\tv_min_i32 %0, %3, %0\n\tv_mad_u32_u24 %0, %0, %4, %5\n\t"
-                 "s_nop 4\n\tglobal_load_lds_dwordx4 %0, %6"
-                 : "=&v"(off)
-                 : "s"(first), "v"(ld_row), "s"(last), "s"(pitch), "v"(col_b), "s"(uniform_ptr(base)),
-                   "{m0}"(__builtin_amdgcn_readfirstlane(lds_addr))
-                 : "memory");
-}
-
-// Direct load of one 16-byte chunk per lane at base + off + add (a gathered
-// row: off is the lane's row offset plus its chunk, add the stage's K offset).
-__device__ __forceinline__ void lds_dma16_at(const void* base, uint32_t off, uint32_t add, uint32_t lds_addr) {
-    uint32_t v;
-    asm volatile("v_add_u32 %0, %1, %2\n\ts_nop 4\n\tglobal_load_lds_dwordx4 %0, %3"
-                 : "=&v"(v)
-                 : "v"(off), "s"(add), "s"(uniform_ptr(base)), "{m0}"(__builtin_amdgcn_readfirstlane(lds_addr))
+// stages); the kernel waits on them explicitly.  Because the compiler does not
+// see the instruction, it also does not insert the wait states the hardware
+// needs before it: a VALU write of an SGPR (v_readfirstlane of the base, or a
+// reload of a spilled scalar) needs 5 wait states before a vector-memory
+// instruction reads it, and an SALU write of M0 needs 1 before an LDS DMA.  The
+// statement copies the base with s_mov_b64, which waits for the VALU write by
+// itself, is no hazard for the load, and separates it from the M0 write: 3
+// issue slots, where an s_nop 4 took 7.
+__device__ __forceinline__ void lds_dma16(const void* base, uint32_t off, uint32_t lds_addr) {
+    uint64_t b;
+    asm volatile("s_mov_b64 %0, %2\n\tglobal_load_lds_dwordx4 %1, %0"
+                 : "=&s"(b)
+                 : "v"(off), "s"(uniform_ptr(base)), "{m0}"(__builtin_amdgcn_readfirstlane(lds_addr))
                  : "memory");
 }
 
@@ -159,7 +133,7 @@ __device__ __forceinline__ void lds_dma16_at(const void* base, uint32_t off, uin
 // reads (16 consecutive rows, one chunk) then hit distinct banks for both 128-
 // and 256-byte bank windows.
 constexpr int kStageK = 64;                 // K per stage
-constexpr int kStages = 2;                  // double buffer: prefetch distance 1
+constexpr int kStages = 2;                  // stage kt lives in buffer kt % 2
 constexpr int kRowB = kStageK * 2;          // bytes per LDS row
 constexpr int kChunks = kRowB / 16;         // 16-byte chunks per row
 
@@ -177,11 +151,6 @@ __device__ __forceinline__ void block_barrier() {
     asm volatile("" ::: "memory");
 }
 
-// Wait until every vector-memory operation of this wave has completed: its
-// direct-to-LDS loads have landed in LDS (the compiler does not see them, so
-// it inserts no wait of its own).
-__device__ __forceinline__ void wait_loads() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
-
 typedef __attribute__((address_space(3))) void lds_void;
 
 
@@ -195,16 +164,15 @@ constexpr int kMI = kWM / 16, kNJ = kWN / 16;         // 16 x 16 MFMA blocks per
 constexpr int kRowsPerLoad = 1024 / kRowB;            // rows one wave-wide 16-byte load covers
 constexpr int kALd = kBM / kRowsPerLoad / kNL;        // direct loads per loader wave per stage
 constexpr int kBLd = kBN / kRowsPerLoad / kNL;
-constexpr int kBRun = kBLd / 2;                       // a loader's B rows: two runs of 32
 constexpr int kStageBytes = (kBM + kBN) * kRowB;
 static_assert(kNL % 4 == 0, "one loader and one storer wave per SIMD");
 static_assert(kBM % (kRowsPerLoad * kNL) == 0 && kBN % (kRowsPerLoad * kNL) == 0, "load split");
 static_assert(kALd + kBLd <= 60, "loads per stage must fit the vmcnt field");
 static_assert(kWN % 64 == 0, "gate/up pairs need 64-column wave tiles");
-static_assert(kBRun * kRowsPerLoad == 32, "a gate/up loader covers one 32-row W1/W3 pair");
+static_assert(kNL == 4 && kBLd == 8 && kRowsPerLoad == 8, "a loader takes 16 rows of each B quarter");
+static_assert(kMI == 4 && kNJ == 8, "quarters of two B blocks, A blocks in pairs");
 static_assert(kALd * kRowsPerLoad == kWM, "loader wave w loads the A rows that waves of row w read");
 static_assert(kStageK == 64, "a stage is two MFMA K steps of 32");
-static_assert(kNJ >= kMI, "the next step's A fragments are read after the first kMI B blocks");
 static_assert(kStages == 2, "staging lives in stage buffer 1");
 
 // Per-lane constants of the direct loads and the fragment reads.
@@ -229,6 +197,13 @@ __device__ __forceinline__ LaneMap lane_map(int lane) {
     return m;
 }
 
+// The same value, opaque to the compiler: what is derived from it is formed
+// where it is used, per tile, and not kept in registers across the K loop.
+__device__ __forceinline__ int opaque(int v) {
+    asm volatile("" : "+v"(v));
+    return v;
+}
+
 // Fragments and MFMAs.  One MFMA K step is K = 32 (two per stage).  Lane
 // (r, g) = (lane % 16, lane / 16) reads row r of each 16-row block at 16-byte
 // chunk 4 ks + kc(g) of K step ks, kc = (0, 2, 1, 3) (8 consecutive K; A and
@@ -238,63 +213,239 @@ __device__ __forceinline__ LaneMap lane_map(int lane) {
 // 16 j + 4 q + 0..3 of tile row 16 i + r.
 __device__ __forceinline__ const bf16x8& frag_at(const uint8_t* p) { return *reinterpret_cast<const bf16x8*>(p); }
 
-// One K step of a wave's 64 x 128 block: its kMI x kNJ MFMAs, B block outer.
-// With rd, the fragments of the next K step (K step nks of the stage at nst)
-// are read between them: B fragment j into b[j] right after the last MFMA
-// that uses it, and the A fragments into the other set an (after the first
-// kMI B blocks), so one step's MFMAs cover the next step's LDS latency with
-// 64 fragment registers per lane.
-__device__ __forceinline__ void k_step(const bf16x8 (&ac)[kMI], bf16x8 (&an)[kMI], bf16x8 (&b)[kNJ],
-                                       f32x4 (&acc)[kMI][kNJ], const uint8_t* nst, int nks, int wm, int wn,
-                                       const LaneMap& lm, bool rd) {
-    const int pc = ((4 * nks + lm.fr_kc) ^ lm.fr_swz) << 4;
-    const uint8_t* sa = nst + (wm * kWM + lm.fr_row) * kRowB + pc;
-    const uint8_t* sb = nst + (kBM + wn * kWN + lm.fr_row) * kRowB + pc;
-#pragma unroll
-    for (int j = 0; j < kNJ; ++j) {
-#pragma unroll
-        for (int i = 0; i < kMI; ++i)
-            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b[j], ac[i], acc[i][j], 0, 0, 0);
-        if (rd) {
-            if (j < kMI) an[j] = frag_at(sa + j * 16 * kRowB);
-            b[j] = frag_at(sb + j * 16 * kRowB);
-        }
-    }
-    static_for<kNJ>([&](auto J) {
-        constexpr int j = decltype(J)::value;
-        __builtin_amdgcn_sched_group_barrier(0x008, kMI, 0);                 // block j's MFMAs
-        __builtin_amdgcn_sched_group_barrier(0x100, j < kMI ? 2 : 1, 0);     // its fragment reads
-    });
+// Loads of one tile for one loader wave.  A: rows wave * 64 .. + 63, 8 loads a
+// stage (lane l of load i: byte offset a_off[i] from the operand base: a tile
+// row, clamped to the expert's last, or a gathered row of x).  B: of quarter q
+// (rows wn * 128 + 32 q .. + 31 of both wave columns wn) the 16 rows wn =
+// wave / 2, 16 (wave % 2) ..: 2 loads a quarter.  The pointers run along K:
+// a and b0 / b1 (quarters 0, 1) one stage ahead of c0 / c1 (quarters 2, 3).
+struct Loads {
+    const char *a, *b0, *b1, *c0, *c1;
+    uint32_t a_off[kALd];
+    uint32_t b_off[2];
+};
+
+template <int I>
+__device__ __forceinline__ void load_a(const Loads& s, uint32_t a_lds, int buf) {
+    lds_dma16(s.a, s.a_off[I], a_lds + buf * kStageBytes + I * 1024);
+}
+// load I = 0..3 of quarters 0, 1 (half 0) or 2, 3 (half 1)
+template <int HALF, int I>
+__device__ __forceinline__ void load_b(const Loads& s, uint32_t b_lds, int buf) {
+    const char* p = HALF ? (I / 2 ? s.c1 : s.c0) : (I / 2 ? s.b1 : s.b0);
+    lds_dma16(p, s.b_off[I % 2],
+              b_lds + buf * kStageBytes + (HALF * 64 + (I / 2) * 32 + (I % 2) * kRowsPerLoad) * kRowB);
+}
+__device__ __forceinline__ void step_half0(Loads& s) { s.a += kRowB; s.b0 += kRowB; s.b1 += kRowB; }
+__device__ __forceinline__ void step_half1(Loads& s) { s.c0 += kRowB; s.c1 += kRowB; }
+__device__ __forceinline__ void load_half0(Loads& s, uint32_t a_lds, uint32_t b_lds, int buf) {
+    static_for<kALd>([&](auto I) { load_a<I.value>(s, a_lds, buf); });
+    static_for<4>([&](auto I) { load_b<0, I.value>(s, b_lds, buf); });
+    step_half0(s);
+}
+__device__ __forceinline__ void load_half1(Loads& s, uint32_t b_lds, int buf) {
+    static_for<4>([&](auto I) { load_b<1, I.value>(s, b_lds, buf); });
+    step_half1(s);
 }
 
-// The K loop of one tile: KT stages of K = 64 (two K steps each).
-// sync(kt) makes stage kt visible and issues the loads of stage kt + 1 (the
-// loaders' wait for their own loads, the workgroup barrier, the next issue and
-// any per-stage bookkeeping of the caller).  A wave's fragment reads run one K
-// step ahead of its MFMAs; the barrier of stage kt + 1 comes after the reads of
-// stage kt's second K step have returned (so the loads issued after it may
-// overwrite stage kt's buffer) and before that step's MFMAs.  A wave whose
-// 64 rows all lie past the tile's valid rows (active = false) computes
-// nothing: its accumulators stay zero and are never stored.
-template <typename Sync>
-__device__ __forceinline__ void k_loop(int KT, const uint8_t* lds, int wm, int wn, const LaneMap& lm, bool active,
-                                       f32x4 (&acc)[kMI][kNJ], Sync&& sync) {
-    bf16x8 a0[kMI], a1[kMI], b[kNJ];
-    sync(0);
-    if (active) {
-        const int pc = (lm.fr_kc ^ lm.fr_swz) << 4;
+// The K loop of one tile: KT stages of K = 64 (KT is even: d % 256 == 0 and
+// inter % 128 == 0), stage kt in buffer kt % 2.  A stage is computed in four
+// quarters (Q = 0..3: all A blocks with B blocks 2 Q, 2 Q + 1), and each
+// quarter's B fragments are read during the quarter before it (two register
+// sets in turn).  The A fragments of the next stage replace this one's in
+// place: blocks 0, 1 after their last MFMA in quarter 3, blocks 2, 3 at the
+// start of the next quarter 0.  So a part of a stage stays in LDS only while
+// one or two quarters read it, and its space takes the loads of the stage two
+// ahead from then on:
+//   barrier a (after quarter 0):  A and B quarters 0, 1 of stage kt are read;
+//                                 B quarters 2, 3 of stage kt are complete.
+//   barrier c (after quarter 2):  B quarters 2, 3 of stage kt are read; A and
+//                                 B quarters 0, 1 of stage kt + 1 are complete.
+// A quarter is four groups of four MFMAs; a group starts with its fragment
+// reads and ends, in a loader wave, with its direct loads, spread so that the
+// address path takes them while the MFMAs run: A of stage kt + 2 in quarters
+// 1, 2, its B quarters 0, 1 in quarter 3, its B quarters 2, 3 in quarter 0 of
+// stage kt + 1.
+//   hook(step)       bookkeeping of the caller, none of it in the middle of the
+//                    loop: after barrier a of the first (kFirst) and second
+//                    stage (kSecond; both only if KT > 2), of the last but one
+//                    (kLast2), before (kPreLast) and after (kLast) that of the
+//                    last.
+// On entry stage 0 has been issued whole; on return every wave is past its
+// last LDS read of the tile (barrier c of the last stage), and buffer 0 was
+// free from barrier a of the last stage (the hook may issue the next tile's
+// stage 0).
+// What bounds it: the board's power at 1.8 GHz (MFMA pipes 72 % busy on the
+// 33,234 rows of d = 7168, inter = 2048, where loading each stage whole behind
+// one barrier kept them 63 % busy), then the LDS, whose fragment reads and
+// direct writes need 256 KB a stage, the time of its MFMAs at 128 bytes a
+// clock.  That call 2328 -> 2131 us, 44,420 rows of d = 2048, inter = 768
+// 393 -> 358 us, 3,001 rows of d = 2048, inter = 1408 98 -> 89 us.  Issuing
+// twelve of a stage's sixteen loads in quarters 1 and 2 was no faster, nor a
+// raised wave priority around the MFMAs or for the loaders (0 to 2 % slower).
+// A wave whose 64 rows all lie past the tile's valid rows (active =
+// false) computes nothing: its accumulators stay zero and are never stored.
+template <int N>
+__device__ __forceinline__ void wait_vm() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
+
+// acc += b a^T in place, as inline assembly: with most of the registers taken,
+// the register allocator otherwise moves accumulators about (24 spilled
+// registers and copies at every tile's end; 2172 -> 2131 us on the 33,234 rows
+// of d = 7168, inter = 2048, 372 -> 358 us on 44,420 rows of d = 2048, inter =
+// 768).  The compiler inserts no wait states around it: acc_pin and the s_nop
+// before and after the K loop separate the MFMAs from the code that writes and
+// reads the accumulators; fragment operands come from LDS reads, whose wait it
+// does insert.
+__device__ __forceinline__ void mfma_acc(f32x4& acc, const bf16x8& b, const bf16x8& a) {
+    asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+v"(acc) : "v"(b), "v"(a));
+}
+__device__ __forceinline__ void acc_pin(f32x4 (&acc)[kMI][kNJ]) {
 #pragma unroll
-        for (int i = 0; i < kMI; ++i) a0[i] = frag_at(lds + (wm * kWM + i * 16 + lm.fr_row) * kRowB + pc);
+    for (int i = 0; i < kMI; ++i)
 #pragma unroll
-        for (int j = 0; j < kNJ; ++j) b[j] = frag_at(lds + (kBM + wn * kWN + j * 16 + lm.fr_row) * kRowB + pc);
+        for (int j = 0; j < kNJ; ++j) asm volatile("" : "+v"(acc[i][j]));
+}
+enum KStep { kMiddle, kFirst, kSecond, kLast2, kPreLast, kLast };
+
+template <bool LOADER, bool ACTIVE, typename Hook>
+__device__ __forceinline__ void k_loop(int KT, const uint8_t* lds, int wm, int wn, int lane, f32x4 (&acc)[kMI][kNJ], Loads& ld, uint32_t a_lds, uint32_t b_lds,
+                                       Hook&& hook) {
+    bf16x8 a[kMI][2], b0[2][2], b1[2][2];
+    const LaneMap lm = lane_map(opaque(lane));
+    const int pc0 = (lm.fr_kc ^ lm.fr_swz) << 4, pc1 = pc0 ^ 64;
+    const uint8_t* const la = lds + (wm * kWM + lm.fr_row) * kRowB;
+    const uint8_t* const lb = lds + (kBM + wn * kWN + lm.fr_row) * kRowB;
+    // fragment n = 0..3 of A blocks i0, i0 + 1 / of quarter q: K step n / 2
+    auto read_a = [&](int buf, int i0, auto Nn) {
+        constexpr int n = decltype(Nn)::value;
+        a[i0 + n % 2][n / 2] = frag_at(la + buf * kStageBytes + (i0 + n % 2) * 16 * kRowB + (n / 2 ? pc1 : pc0));
+    };
+    auto read_b = [&](bf16x8 (&b)[2][2], int buf, int q, auto Nn) {
+        constexpr int n = decltype(Nn)::value;
+        b[n % 2][n / 2] = frag_at(lb + buf * kStageBytes + (2 * q + n % 2) * 16 * kRowB + (n / 2 ? pc1 : pc0));
+    };
+    // MFMA group g = 0..3 of quarter Q.  Quarters 1, 2: K step g / 2, A blocks
+    // 2 (g % 2) ..; quarters 0, 3: A blocks 2 (g / 2) .., K step g % 2 (the A
+    // fragments change hands half way).
+    auto mfma4 = [&](bf16x8 (&b)[2][2], auto Qn, auto Gn) {
+        constexpr int q = decltype(Qn)::value, g = decltype(Gn)::value;
+        constexpr bool by_k = q == 1 || q == 2;
+        constexpr int ks = by_k ? g / 2 : g % 2, i0 = 2 * (by_k ? g % 2 : g / 2);
+#pragma unroll
+        for (int i = i0; i < i0 + 2; ++i)
+#pragma unroll
+            for (int jj = 0; jj < 2; ++jj)
+                mfma_acc(acc[i][2 * q + jj], b[jj][ks], a[i][ks]);
+    };
+    auto N0 = std::integral_constant<int, 0>{};
+    auto N1 = std::integral_constant<int, 1>{};
+    auto N2 = std::integral_constant<int, 2>{};
+    auto N3 = std::integral_constant<int, 3>{};
+    acc_pin(acc);
+    asm volatile("s_nop 7");
+    if (LOADER) wait_vm<0>();
+    block_barrier();                                   // stage 0 visible; buffer 1 free
+    if (LOADER) load_half0(ld, a_lds, b_lds, 1);
+    if constexpr (ACTIVE)
+        static_for<4>([&](auto N) {
+            read_b(b0, 0, 0, N);
+            read_a(0, 0, N);
+        });
+    auto stage = [&](auto BUF, auto STEP) {
+        constexpr int buf = decltype(BUF)::value;
+        constexpr KStep step = decltype(STEP)::value;
+        constexpr bool next1 = step != kLast, next2 = next1 && step != kLast2;   // stages kt + 1, kt + 2 exist
+        static_for<4>([&](auto G) {                                            // quarter 0
+            if constexpr (ACTIVE) {
+                if constexpr (G.value < 2) {
+                    read_a(buf, 2, std::integral_constant<int, 2 * G.value>{});
+                    read_a(buf, 2, std::integral_constant<int, 2 * G.value + 1>{});
+                } else {
+                    read_b(b1, buf, 1, std::integral_constant<int, 2 * G.value - 4>{});
+                    read_b(b1, buf, 1, std::integral_constant<int, 2 * G.value - 3>{});
+                }
+                mfma4(b0, N0, G);
+            }
+            if constexpr (LOADER && next1) load_b<1, G.value>(ld, b_lds, buf ^ 1);
+            __builtin_amdgcn_sched_barrier(0);
+        });
+        if constexpr (LOADER && next1) step_half1(ld);
+        if constexpr (step == kLast) hook(std::integral_constant<KStep, kPreLast>{});
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");       // A, quarters 0 and 1 read
+        if constexpr (LOADER) {                                  // quarters 2, 3 of stage kt landed
+            wait_vm<next1 ? kALd + 8 : 0>();
+        }
+        block_barrier();                                         // barrier a
+        if constexpr (step != kMiddle) hook(STEP);
+        static_for<4>([&](auto G) {                                            // quarter 1
+            if constexpr (ACTIVE) {
+                read_b(b0, buf, 2, G);
+                mfma4(b1, N1, G);
+            }
+            if constexpr (LOADER && next2) load_a<G.value>(ld, a_lds, buf);
+            __builtin_amdgcn_sched_barrier(0);
+        });
+        static_for<4>([&](auto G) {                                            // quarter 2
+            if constexpr (ACTIVE) {
+                read_b(b1, buf, 3, G);
+                mfma4(b0, N2, G);
+            }
+            if constexpr (LOADER && next2) load_a<4 + G.value>(ld, a_lds, buf);
+            __builtin_amdgcn_sched_barrier(0);
+        });
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");       // quarters 2, 3 read
+        if constexpr (LOADER && next1) {                         // A, quarters 0, 1 of stage kt + 1 landed
+            wait_vm<next2 ? kALd + 4 : 4>();
+        }
+        block_barrier();                                         // barrier c
+        static_for<4>([&](auto G) {                                            // quarter 3
+            if constexpr (ACTIVE) {
+                if constexpr (next1) {
+                    if constexpr (G.value < 2) {
+                        read_b(b0, buf ^ 1, 0, std::integral_constant<int, 2 * G.value>{});
+                        read_b(b0, buf ^ 1, 0, std::integral_constant<int, 2 * G.value + 1>{});
+                    } else if constexpr (G.value == 2) {
+                        static_for<4>([&](auto N) { read_a(buf ^ 1, 0, N); });
+                    }
+                }
+                mfma4(b1, N3, G);
+            }
+            if constexpr (LOADER && next2) load_b<0, G.value>(ld, b_lds, buf);
+            __builtin_amdgcn_sched_barrier(0);
+        });
+        if constexpr (LOADER && next2) step_half0(ld);
+    };
+    int kt = 0;
+    if constexpr (!LOADER) {
+        if (KT > 2) {
+            stage(N0, std::integral_constant<KStep, kFirst>{});
+            stage(N1, std::integral_constant<KStep, kSecond>{});
+            kt = 2;
+        }
     }
-    for (int kt = 0; kt < KT; ++kt) {
-        if (active) k_step(a0, a1, b, acc, lds + (kt % kStages) * kStageBytes, 1, wm, wn, lm, true);
-        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");       // stage kt fully read
-        // stage kt + 1 visible (after the last stage: a plain barrier; the
-        // fragments read after it are never used)
-        sync(kt + 1);
-        if (active) k_step(a1, a0, b, acc, lds + ((kt + 1) % kStages) * kStageBytes, 0, wm, wn, lm, true);
+    for (; kt + 2 < KT; kt += 2) {
+        stage(N0, std::integral_constant<KStep, kMiddle>{});
+        stage(N1, std::integral_constant<KStep, kMiddle>{});
+    }
+    stage(N0, std::integral_constant<KStep, kLast2>{});
+    stage(N1, std::integral_constant<KStep, kLast>{});
+    asm volatile("s_nop 15\n\ts_nop 15");             // the last MFMAs' results are written
+    acc_pin(acc);
+}
+
+// The four roles of a wave in a tile (wave-uniform): each has a loop of its
+// own, all with the same barriers.
+template <typename LoadHook, typename StoreHook>
+__device__ __forceinline__ void run_k_loop(int KT, const uint8_t* lds, int wm, int wn, int lane,
+                                           bool loader, bool active, f32x4 (&acc)[kMI][kNJ], Loads& ld,
+                                           uint32_t a_lds, uint32_t b_lds, LoadHook&& load_hook,
+                                           StoreHook&& store_hook) {
+    if (loader) {
+        if (active) k_loop<true, true>(KT, lds, wm, wn, lane, acc, ld, a_lds, b_lds, load_hook);
+        else k_loop<true, false>(KT, lds, wm, wn, lane, acc, ld, a_lds, b_lds, load_hook);
+    } else {
+        if (active) k_loop<false, true>(KT, lds, wm, wn, lane, acc, ld, a_lds, b_lds, store_hook);
+        else k_loop<false, false>(KT, lds, wm, wn, lane, acc, ld, a_lds, b_lds, store_hook);
     }
 }
 
@@ -360,10 +511,7 @@ __device__ __forceinline__ void store_tile(const f32x4 (&acc)[kMI][kNJ], uint16_
     auto stg_swz = [](int r) { return (r / OUT_RPW) & (OUT_CH - 1); };
     const bool loader = wave < kNL;
     const int wm = wave / kWavesN, wn = wave % kWavesN;
-    // the lane index is made opaque so that lane-derived addresses are formed
-    // here, per tile, and not kept live across the K loop
-    int ep_lane = lane;
-    asm volatile("" : "+v"(ep_lane));
+    const int ep_lane = opaque(lane);
     const int ep_row = ep_lane & 15, ep_q = ep_lane >> 4;
     const int ep_c = 2 * (ep_q & 1) + (ep_q >> 1);     // this lane's chunk within a pair's four
     uint8_t* my_stg = staging + (loader ? wave : 0) * STG_B;
@@ -440,89 +588,42 @@ __device__ __forceinline__ void store_tile(const f32x4 (&acc)[kMI][kNJ], uint16_
     }
 }
 
-// Operand sources of one tile for one loader wave: A rows (or, gathered, the
-// base of x) and the wave's two 32-row B runs; pitch = bytes per operand row.
-struct TileSrc {
-    const char* a;
-    const char* b[2];
-    uint32_t pitch, blk;                 // row pitch; bytes per 8-row block
-    int rows;                            // valid A rows (past them: the last row again)
-};
-
-// Issues one stage's direct-to-LDS loads of a loader wave into stage buffer
-// kt % 2: A rows wave * 64 .. + 63 and the wave's 64 B rows.  a_off holds the
-// per-lane byte offsets of gathered A rows (gathered = true).
-__device__ __forceinline__ void issue_stage(const TileSrc& s, int kt, int wave, const LaneMap& lm,
-                                            const uint32_t (&lane_off)[2], bool gathered,
-                                            const uint32_t* a_off, uint32_t lds_base) {
-    const uint32_t st = lds_base + static_cast<uint32_t>((kt % kStages) * kStageBytes);
-    const uint32_t kb = static_cast<uint32_t>(kt) * kStageK * 2;
-    const uint32_t a_lds = st + wave * kALd * 1024;
-    const int a_first = wave * kALd * kRowsPerLoad;
-    if (a_first >= s.rows) {
-        // no valid row in this wave's 64 A rows: the waves that would read them
-        // compute nothing (k_loop's active flag), so they are not loaded
-    } else if (gathered) {
-        static_for<kALd>([&](auto I) { lds_dma16_at(s.a, a_off[I.value], kb, a_lds + I.value * 1024); });
-    } else if (a_first + kALd * kRowsPerLoad <= s.rows) {                 // wave-uniform
-        const char* a_base = s.a + kb + static_cast<size_t>(wave * kALd) * s.blk;
-        static_for<kALd>([&](auto I) {
-            lds_dma16_blk<I.value>(a_base, lane_off[(wave * kALd + I.value) & 1], s.blk, a_lds + I.value * 1024);
-        });
-    } else {
-        // the last tile of an expert: rows past its end repeat its last row
-        static_for<kALd>([&](auto I) {
-            lds_dma16_clamped(s.a + kb, lm.ld_row, a_first + I.value * kRowsPerLoad, s.rows - 1, s.pitch,
-                              lm.col_b[(wave * kALd + I.value) & 1], a_lds + I.value * 1024);
-        });
-    }
-    const uint32_t b_lds = st + kBM * kRowB + wave * kBLd * 1024;
-    static_for<kBLd>([&](auto I) {
-        constexpr int i = decltype(I)::value;
-        lds_dma16_blk<i % kBRun>(s.b[i / kBRun] + kb, lane_off[(wave * kBLd + i) & 1], s.blk, b_lds + i * 1024);
-    });
-}
-
-// Sources of tile (expert l, rows [row0, row0 + rows), block column nt) for
-// loader wave lw.  Gate/up: A = x (K = d), B runs = W1 and W3 rows
-// nt * 128 + lw * 32 .. + 31 (the B tile interleaves 32-row blocks of W1 and
-// W3); down: A = H (K = inter), B runs = W2 rows nt * 256 + lw * 64 .. + 63.
-__device__ __forceinline__ TileSrc tile_src(bool gu, bool gathered, const uint16_t* A, const uint16_t* B0,
-                                            const uint16_t* B1, int l, int row0, int rows, int nt, int lw, int K,
-                                            int N_out) {
-    TileSrc s;
-    s.pitch = static_cast<uint32_t>(K) * 2u;
-    s.blk = static_cast<uint32_t>(kRowsPerLoad) * s.pitch;
-    s.rows = rows;
+// Loads of tile (expert l, rows [row0, row0 + rows), block column nt) for
+// loader wave lw, at stage 0.  Gate/up: A = x (K = d; rows of x through
+// row_src if gathered, clamped into [0, x_rows)), B quarters of wave column wn
+// are rows nt * 128 + 64 wn + {0, 32} .. + 31 of W1 (quarters 0, 2) and W3
+// (quarters 1, 3); down: A = H (K = inter), B quarters are rows
+// nt * 256 + 128 wn + 32 q .. + 31 of W2.  Rows past the tile's last valid one
+// repeat it.  Lane byte offsets stay below 2^32 (x_rows * pitch does; a tile
+// spans 256 rows of at most 2^20 bytes).
+__device__ __forceinline__ void tile_loads(Loads& s, bool gu, bool gathered, const uint16_t* A, const uint16_t* B0,
+                                           const uint16_t* B1, int l, int row0, int rows, int nt, int lw, int K,
+                                           int N_out, int lane, const int32_t* __restrict__ row_src,
+                                           int x_rows) {
+    const LaneMap lm = lane_map(opaque(lane));
+    const uint32_t pitch = static_cast<uint32_t>(K) * 2u;
     s.a = gathered ? reinterpret_cast<const char*>(A) : reinterpret_cast<const char*>(A + static_cast<size_t>(row0) * K);
+    const int wn = lw >> 1, h = lw & 1;
     if (gu) {
-        const size_t row = static_cast<size_t>(l) * N_out + nt * (kBN / 2) + lw * 32;
-        s.b[0] = reinterpret_cast<const char*>(B0 + row * K);
-        s.b[1] = reinterpret_cast<const char*>(B1 + row * K);
+        const size_t row = static_cast<size_t>(l) * N_out + nt * (kBN / 2) + wn * (kWN / 2) + h * 16;
+        s.b0 = reinterpret_cast<const char*>(B0 + row * K);
+        s.b1 = reinterpret_cast<const char*>(B1 + row * K);
+        s.c0 = s.b0 + static_cast<size_t>(32) * pitch;
+        s.c1 = s.b1 + static_cast<size_t>(32) * pitch;
     } else {
-        const size_t row = static_cast<size_t>(l) * N_out + nt * kBN + lw * kBLd * kRowsPerLoad;
-        s.b[0] = reinterpret_cast<const char*>(B0 + row * K);
-        s.b[1] = reinterpret_cast<const char*>(B0 + (row + 32) * K);
+        const size_t row = static_cast<size_t>(l) * N_out + nt * kBN + wn * kWN + h * 16;
+        s.b0 = reinterpret_cast<const char*>(B0 + row * K);
+        s.b1 = s.b0 + static_cast<size_t>(32) * pitch;
+        s.c0 = s.b0 + static_cast<size_t>(64) * pitch;
+        s.c1 = s.b0 + static_cast<size_t>(96) * pitch;
     }
-    return s;
-}
-
-// Lane byte offsets of the current tile's loads (pitch-dependent) and, for
-// gathered A, of each A row this lane loads (x row row_src[row0 + r],
-// clamped into [0, x_rows)).
-__device__ __forceinline__ void lane_offsets(const TileSrc& s, const LaneMap& lm, uint32_t (&lane_off)[2]) {
-    lane_off[0] = lm.ld_row * s.pitch + lm.col_b[0];
-    lane_off[1] = lm.ld_row * s.pitch + lm.col_b[1];
-}
-__device__ __forceinline__ void gather_offsets(const TileSrc& s, const LaneMap& lm, int wave, int row0,
-                                               const int32_t* __restrict__ row_src, int x_rows,
-                                               uint32_t (&a_off)[kALd]) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i) s.b_off[i] = (i * kRowsPerLoad + lm.ld_row) * pitch + lm.col_b[i];
 #pragma unroll
     for (int i = 0; i < kALd; ++i) {
-        const int r = min(wave * kALd * kRowsPerLoad + i * kRowsPerLoad + lm.ld_row, s.rows - 1);
-        int tok = row_src[row0 + r];
-        tok = min(max(tok, 0), x_rows - 1);
-        a_off[i] = static_cast<uint32_t>(tok) * s.pitch + lm.col_b[(wave * kALd + i) & 1];
+        int r = min(lw * kALd * kRowsPerLoad + i * kRowsPerLoad + lm.ld_row, rows - 1);
+        if (gathered) r = min(max(row_src[row0 + r], 0), x_rows - 1);
+        s.a_off[i] = static_cast<uint32_t>(r) * pitch + lm.col_b[(lw * kALd + i) & 1];
     }
 }
 
@@ -561,7 +662,8 @@ __global__ __launch_bounds__(kNW * kWave, 1) void ffn_gemm_bf16_kernel(
     const bool loader = wave < kNL;
     const int wm = wave / kWavesN, wn = wave % kWavesN;
     const uint32_t lds_base = static_cast<uint32_t>(reinterpret_cast<uintptr_t>((lds_void*)lds));
-    const LaneMap lm = lane_map(lane);
+    const uint32_t a_lds = lds_base + wave * kALd * 1024;             // loader waves' parts of a stage
+    const uint32_t b_lds = lds_base + (kBM + (wave >> 1) * kWN + (wave & 1) * 16) * kRowB;
     // combine plan of a down tile: each storer lane loads one row's entry at
     // the third stage (after the second, where the fused kernel's storers
     // wait for their previous stores to drain) and writes it to the LDS table
@@ -570,26 +672,23 @@ __global__ __launch_bounds__(kNW * kWave, 1) void ffn_gemm_bf16_kernel(
     const bool comb = !GATEUP && cp.dst != nullptr;
     int pl_d = -1;
     float pl_w = 0.0f;
-    auto load_plan = [&](int kt, int KTn, int r0, int nrows) {
-        const int q = (wave - kNL) * kWave + lane;
-        if (kt == min(2, KTn - 1)) {
+    auto load_plan = [&](auto step, int r0, int nrows) {
+        const int q = (wave - kNL) * kWave + opaque(lane);
+        if constexpr (decltype(step)::value == kLast2) {
             pl_d = -1;
             pl_w = 0.0f;
             if (q < nrows) {
                 pl_d = cp.dst[r0 + q];
                 pl_w = cp.w[r0 + q];
             }
-        }
-        if (kt == KTn - 1) {
+        } else if constexpr (decltype(step)::value == kPreLast) {
             plan_dst[q] = pl_d;
             plan_w[q] = pl_w;
         }
     };
 
     int row0 = 0, rows = 0, nt = 0;
-    TileSrc src;
-    uint32_t lane_off[2] = {0, 0};
-    uint32_t a_off[kALd];
+    Loads ld;
     auto start_tile = [&](int tile) {
         const int m_tile = tile / n_tiles;
         nt = tile % n_tiles;
@@ -598,10 +697,9 @@ __global__ __launch_bounds__(kNW * kWave, 1) void ffn_gemm_bf16_kernel(
         row0 = __builtin_amdgcn_readfirstlane(row_begin[l] + (m_tile - mt_prefix[l]) * kBM);
         rows = __builtin_amdgcn_readfirstlane(min(kBM, row_end[l] - row0));
         if (!loader) return;
-        src = tile_src(GATEUP, GATHER, A, B0, B1, l, row0, rows, nt, wave, K, N_out);
-        lane_offsets(src, lm, lane_off);
-        if constexpr (GATHER) gather_offsets(src, lm, wave, row0, row_src, x_rows, a_off);
-        issue_stage(src, 0, wave, lm, lane_off, GATHER, a_off, lds_base);
+        tile_loads(ld, GATEUP, GATHER, A, B0, B1, l, row0, rows, nt, wave, K, N_out, lane, row_src, x_rows);
+        load_half0(ld, a_lds, b_lds, 0);
+        load_half1(ld, b_lds, 0);
     };
 
     int tile = worker_id();
@@ -615,19 +713,21 @@ __global__ __launch_bounds__(kNW * kWave, 1) void ffn_gemm_bf16_kernel(
 #pragma unroll
                 for (int r = 0; r < 4; ++r) acc[i][j][r] = 0.0f;
 
-        k_loop(KT, lds, wm, wn, lm, wm * kWM < rows, acc, [&](int kt) {
-            if (loader) wait_loads();              // this wave's part of stage kt has landed
-            block_barrier();                       // stage kt visible; the other buffer is free
-            if (loader && kt + 1 < KT) issue_stage(src, kt + 1, wave, lm, lane_off, GATHER, a_off, lds_base);
-            if (comb && !loader) load_plan(kt, KT, row0, rows);
-        });
-
-        // every wave is done with this tile's LDS: loaders start the next
-        // tile's stage 0 (buffer 0), buffer 1 becomes the staging area
-        block_barrier();
         const int cur_row0 = row0, cur_rows = rows, cur_nt = nt;
         const int next = tile + gridDim.x;
-        if (next < total) start_tile(next);
+        // in the last stage buffer 0 is free: the next tile's stage 0 lands
+        // during the rest of that stage and the epilogue
+        auto load_hook = [&](auto step) {
+            if constexpr (decltype(step)::value == kLast) {
+                if (next < total) start_tile(next);
+            }
+        };
+        auto store_hook = [&](auto step) {
+            if (comb) load_plan(step, cur_row0, cur_rows);
+            load_hook(step);
+        };
+        run_k_loop(KT, lds, wm, wn, lane, loader, wm * kWM < rows, acc, ld, a_lds, b_lds, load_hook, store_hook);
+        // buffer 1 is the staging area until the next tile fills its stage 1
         store_tile<GATEUP>(acc, C, N_out, cur_row0, cur_rows, cur_nt, wave, lane, lds + kStageBytes,
                            comb ? plan_dst : nullptr, plan_w, cp.parts, cp.parts_rows);
         tile = next;
@@ -714,22 +814,22 @@ __global__ __launch_bounds__(kNW * kWave, 1) void ffn_fused_bf16_kernel(
     const bool loader = wave < kNL;
     const int wm = wave / kWavesN, wn = wave % kWavesN;
     const uint32_t lds_base = static_cast<uint32_t>(reinterpret_cast<uintptr_t>((lds_void*)lds));
-    const LaneMap lm = lane_map(lane);
+    const uint32_t a_lds = lds_base + wave * kALd * 1024;             // loader waves' parts of a stage
+    const uint32_t b_lds = lds_base + (kBM + (wave >> 1) * kWN + (wave & 1) * 16) * kRowB;
     // combine plan of a down tile (as in the two-kernel path)
     const bool comb = cp.dst != nullptr;
     int pl_d = -1;
     float pl_w = 0.0f;
-    auto load_plan = [&](int kt, int KTn, int r0, int nrows) {
-        const int q = (wave - kNL) * kWave + lane;
-        if (kt == min(2, KTn - 1)) {
+    auto load_plan = [&](auto step, int r0, int nrows) {
+        const int q = (wave - kNL) * kWave + opaque(lane);
+        if constexpr (decltype(step)::value == kLast2) {
             pl_d = -1;
             pl_w = 0.0f;
             if (q < nrows) {
                 pl_d = cp.dst[r0 + q];
                 pl_w = cp.w[r0 + q];
             }
-        }
-        if (kt == KTn - 1) {
+        } else if constexpr (decltype(step)::value == kPreLast) {
             plan_dst[q] = pl_d;
             plan_w[q] = pl_w;
         }
@@ -763,9 +863,7 @@ __global__ __launch_bounds__(kNW * kWave, 1) void ffn_fused_bf16_kernel(
 
     struct Tile { int gu, m, nt, row0, rows, KT; };
     Tile T{};
-    TileSrc src;
-    uint32_t lane_off[2] = {0, 0};
-    uint32_t a_off[kALd];
+    Loads ld;
     auto decode = [&](int t) {
         Tile D;
         D.gu = t < GU ? 1 : 0;
@@ -779,15 +877,15 @@ __global__ __launch_bounds__(kNW * kWave, 1) void ffn_fused_bf16_kernel(
         D.row0 = __builtin_amdgcn_readfirstlane(row_begin[l] + (D.m - mt_prefix[l]) * kBM);
         D.rows = __builtin_amdgcn_readfirstlane(min(kBM, row_end[l] - D.row0));
         if (loader) {
-            src = D.gu ? tile_src(true, GATHER, X, W1, W3, l, D.row0, D.rows, D.nt, wave, d, inter)
-                       : tile_src(false, false, H, W2, nullptr, l, D.row0, D.rows, D.nt, wave, inter, d);
-            lane_offsets(src, lm, lane_off);
-            if (GATHER && D.gu) gather_offsets(src, lm, wave, D.row0, row_src, x_rows, a_off);
+            if (D.gu) tile_loads(ld, true, GATHER, X, W1, W3, l, D.row0, D.rows, D.nt, wave, d, inter, lane, row_src, x_rows);
+            else tile_loads(ld, false, false, H, W2, nullptr, l, D.row0, D.rows, D.nt, wave, inter, d, lane, nullptr, 0);
         }
         return D;
     };
-    auto issue = [&](int kt) {
-        if (loader) issue_stage(src, kt, wave, lm, lane_off, GATHER && T.gu, a_off, lds_base);
+    auto issue0 = [&]() {
+        if (!loader) return;
+        load_half0(ld, a_lds, b_lds, 0);
+        load_half1(ld, b_lds, 0);
     };
     // wave 0 waits until m-tile m's H rows are complete, then the workgroup goes on
     auto wait_ready = [&](int m) {
@@ -826,7 +924,7 @@ __global__ __launch_bounds__(kNW * kWave, 1) void ffn_fused_bf16_kernel(
         if (t < Q) {
             T = decode(t);
             if (!T.gu) wait_ready(T.m);
-            issue(0);
+            issue0();
         }
         while (t < Q) {
             f32x4 acc[kMI][kNJ];
@@ -837,54 +935,60 @@ __global__ __launch_bounds__(kNW * kWave, 1) void ffn_fused_bf16_kernel(
 #pragma unroll
                     for (int r = 0; r < 4; ++r) acc[i][j][r] = 0.0f;
 
-            const int KT = T.KT;
+            const Tile C = T;
+            const int KT = C.KT;
             const bool ahead = KT >= 4;            // claim, publish and poll inside the K loop
-            int claim = 0, poll = 0;
-            k_loop(KT, lds, wm, wn, lm, wm * kWM < T.rows, acc, [&](int kt) {
-                if (loader) wait_loads();
-                block_barrier();
-                if (kt + 1 < KT) issue(kt + 1);
-                if (comb && !T.gu && !loader) load_plan(kt, KT, T.row0, T.rows);
-                if (ahead) {
-                    if (kt == 0 && wave == kNL && lane == 0) claim = atomic_add_agent(queue, 1);
-                    if (kt == 1) {
-                        deliver();
-                        if (wave == kNL) {
-                            if (lane == 0) bcast[0] = claim;
-                            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // visible at the next barrier
-                        }
-                    }
-                    if (kt == KT - 2 && wave == 0) {
-                        const int nx = bcast[0];
-                        if (nx >= GU && nx < Q && lane == 0) {
+            int claim = 0, poll = 0, nx = Q, early = 0;
+            // last stage: buffer 0 is free, and a ready next tile's stage 0
+            // lands during the rest of the stage and the epilogue
+            auto start_next = [&]() {
+                nx = __builtin_amdgcn_readfirstlane(bcast[0]);
+                early = __builtin_amdgcn_readfirstlane(bcast[1]);
+                if (nx < Q) {
+                    T = decode(nx);
+                    if (early) issue0();
+                }
+            };
+            const bool active = wm * kWM < C.rows;
+            auto load_hook = [&](auto step) {
+                if constexpr (decltype(step)::value == kLast) {
+                    if (ahead) start_next();
+                }
+            };
+            auto store_hook = [&](auto step) {
+                constexpr KStep at = decltype(step)::value;
+                if (comb && !C.gu) load_plan(step, C.row0, C.rows);
+                if constexpr (at == kSecond) deliver();
+                if (ahead && wave == kNL && lane == 0) {
+                    if constexpr (at == kFirst) claim = atomic_add_agent(queue, 1);
+                    if constexpr (at == kLast2) {
+                        if (claim >= GU && claim < Q) {
                             int m_off, nt;
-                            entry_tile(nx - GU, n_dn, m_off, nt);
+                            entry_tile(claim - GU, n_dn, m_off, nt);
                             poll = atomic_add_agent(ready + mb + m_off, 0);
                         }
                     }
+                    if constexpr (at == kPreLast) {
+                        bcast[0] = claim;
+                        bcast[1] = (claim < GU || claim >= Q || poll >= target) ? 1 : 0;
+                    }
                 }
-            });
-            if (ahead && wave == 0 && lane == 0) {
-                const int nx = bcast[0];
-                bcast[1] = (nx < GU || nx >= Q || poll >= target) ? 1 : 0;
-            }
-            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-            block_barrier();                       // every wave is done with this tile's LDS
+                load_hook(step);
+            };
+            run_k_loop(KT, lds, wm, wn, lane, loader, active, acc, ld, a_lds, b_lds, load_hook, store_hook);
             if (!ahead) {
                 deliver();
-                if (wave == kNL && lane == 0) {
-                    bcast[0] = atomic_add_agent(queue, 1);
-                    bcast[1] = 0;
-                }
+                if (wave == kNL && lane == 0) bcast[0] = atomic_add_agent(queue, 1);
                 asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
                 block_barrier();
-            }
-            const int nx = __builtin_amdgcn_readfirstlane(bcast[0]);
-            const int early = __builtin_amdgcn_readfirstlane(bcast[1]) | (nx < GU ? 1 : 0);
-            const Tile C = T;
-            if (nx < Q) {
-                T = decode(nx);
-                if (early) issue(0);
+                nx = __builtin_amdgcn_readfirstlane(bcast[0]);
+                if (nx < Q) {
+                    T = decode(nx);
+                    if (nx < GU) {
+                        early = 1;
+                        issue0();
+                    }
+                }
             }
             if (C.gu) store_tile<true>(acc, H, inter, C.row0, C.rows, C.nt, wave, lane, lds + kStageBytes);
             else store_tile<false>(acc, Y, d, C.row0, C.rows, C.nt, wave, lane, lds + kStageBytes,
@@ -893,7 +997,7 @@ __global__ __launch_bounds__(kNW * kWave, 1) void ffn_fused_bf16_kernel(
             if (nx < Q && !early) {
                 deliver();                         // the next tile may need this tile's rows
                 wait_ready(T.m);
-                issue(0);
+                issue0();
             }
             t = nx;
         }
