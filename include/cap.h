@@ -324,7 +324,9 @@ cap_status cap_permute(const cap_topology *topo, cap_permute_mode mode, int32_t 
  * bf16 calls with max_rows >= 8192 run both GEMMs in one kernel with a tile
  * queue per XCD (a down tile starts once the gate/up tiles of its rows are
  * done) on a device of 8 XCDs (or one); other calls run one kernel per GEMM.
- * Both give the same bits.  The fused kernel's waits between workgroups are
+ * In either, a call whose experts turn out (on the device) to hold few rows
+ * each runs both GEMMs on narrow tiles, one kernel after the other.  All give
+ * the same bits.  The fused kernel's waits between workgroups are
  * bounded; one that gives up leaves that call's output invalid and is counted
  * only where cap_expert_ffn_ex is given a counter (cap_ffn_options).
  */
@@ -370,6 +372,7 @@ cap_status cap_expert_ffn_gather(cap_dtype dtype, int32_t E_loc, int32_t d, int3
  *                       and gives up after spin_limit polls, every kernel
  *                       still finishes, the output is invalid and
  *                       *wait_errors grows by the number of down tiles.
+ * Calls with max_workgroups or force_wait_timeout never take narrow tiles.
  */
 typedef struct {
     int32_t *wait_errors;

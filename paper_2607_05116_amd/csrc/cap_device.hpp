@@ -18,8 +18,9 @@ constexpr size_t kLayoutScratchBytes = size_t(4) << 20;   // cap_dispatch_layout
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
-// 16-byte raw vector (native clang vector: stays in registers, unlike HIP's uint4 struct)
+// 16- and 8-byte raw vectors (native clang vector: stay in registers, unlike HIP's uint4 struct)
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
 // bf16 <-> fp32 on raw 16-bit patterns.
 __device__ __forceinline__ float bf16_to_f32(uint16_t b) {

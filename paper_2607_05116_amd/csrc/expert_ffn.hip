@@ -21,10 +21,12 @@
 //   * Each wave reads its LDS fragments a quarter of a stage ahead of its MFMAs
 //     (16 x 16 x 32 MFMAs: half the accumulator reads and writes per flop of
 //     the 32 x 32 x 16 form, measured 3-4 % faster on whole calls).
-//   * Calls of many m-tiles run both GEMMs in one persistent kernel with a
-//     tile queue per XCD (ffn_fused_bf16_kernel); calls of few m-tiles run one
-//     persistent kernel per GEMM (ffn_gemm_bf16_kernel).  Every output element
-//     takes the same arithmetic in both, so the two give identical bits.
+//   * Calls of many rows' capacity run both GEMMs in one persistent kernel with
+//     a tile queue per XCD (ffn_fused_bf16_kernel); others run one persistent
+//     kernel per GEMM (ffn_gemm_bf16_kernel).  In either, a call whose experts
+//     turn out to hold few rows each runs on narrow tiles (narrow_gemm).  Every
+//     output element takes the same arithmetic in all of them, so they give
+//     identical bits.
 //   * Optionally (a combine plan) the down GEMM's epilogue writes the rows of
 //     tokens with a single kept expert on the rank, scaled by their gate
 //     weight, into the receive-side buffer instead of Y (Sec. II-C local
@@ -83,8 +85,14 @@ __device__ __forceinline__ int find_expert(const int* mt_prefix, int E_loc, int 
     return lo;
 }
 
-__device__ __forceinline__ int worker_id() {
-    const int G = gridDim.x, b = blockIdx.x;
+// Workgroups that take part in `total` tiles (a whole round of XCDs more than
+// the tiles at most: the rest of the grid has nothing to do), and this one's
+// place among them, or -1.  Block b runs on XCD b % 8, so each XCD gets a
+// contiguous run of places, and few tiles spread over all XCDs.
+__device__ __forceinline__ int worker_count(int total) { return min(static_cast<int>(gridDim.x), (total + 7) & ~7); }
+__device__ __forceinline__ int worker_id(int G) {
+    const int b = blockIdx.x;
+    if (b >= G) return -1;
     return (G % 8 == 0) ? (b % 8) * (G / 8) + b / 8 : b;
 }
 
@@ -461,18 +469,18 @@ struct CombinePlan {
     int parts_rows;
 };
 
-// One 16-byte chunk (8 bf16 of a Y row) scaled by w the way the destination
-// reduce does it for a single term: fp32 fmaf(w, y, 0), then bf16 rounded to
-// nearest even (the hardware conversion gives the reduce's bits for finite
-// values).
+// Two bf16 of a Y row scaled by w the way the destination reduce does it for a
+// single term: fp32 fmaf(w, y, 0), then bf16 rounded to nearest even (the
+// hardware conversion gives the reduce's bits for finite values); and a 16-byte
+// chunk of them.
+__device__ __forceinline__ uint32_t scale_pair(uint32_t v, float w) {
+    return pack_bf16x2_rne(__builtin_fmaf(w, __uint_as_float(v << 16), 0.0f),
+                           __builtin_fmaf(w, __uint_as_float(v & 0xFFFF0000u), 0.0f));
+}
 __device__ __forceinline__ u32x4 scale_chunk(const u32x4& v, float w) {
     u32x4 o;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const float lo = __builtin_fmaf(w, __uint_as_float(v[i] << 16), 0.0f);
-        const float hi = __builtin_fmaf(w, __uint_as_float(v[i] & 0xFFFF0000u), 0.0f);
-        o[i] = pack_bf16x2_rne(lo, hi);
-    }
+    for (int i = 0; i < 4; ++i) o[i] = scale_pair(v[i], w);
     return o;
 }
 
@@ -627,6 +635,307 @@ __device__ __forceinline__ void tile_loads(Loads& s, bool gu, bool gathered, con
     }
 }
 
+// ------------------------------------------------------------------ narrow tiles (few rows per expert)
+// A call whose experts hold few rows each (decode, small chunks) reads every
+// weight once for little arithmetic: what bounds it is the weights' way from
+// HBM.  256 x 256 tiles then leave most of the chip idle (an expert has 16
+// gate/up tiles at inter = 2048) and keep too little in flight.  On narrow
+// tiles, 257 rows over 8 experts of d = 7168, inter = 2048 take 146 us where wide
+// tiles take 194 (705 MB of weights: 4.8 TB/s; a large copy moves 5.2 TB/s), 61
+// rows over 16 experts of d = 2048, inter = 768 39 us instead of 59.
+// Narrow tiles are BM = 64 or 128 rows x 128 weight rows (64 H columns of
+// gate/up, or 128 output columns), run by the same eight waves with a ring of
+// K = 64 stages (five of 24 KB, or four of 32 KB), all but one of them in
+// flight, that runs on across the tiles of a workgroup.  Every wave loads an
+// eighth of a stage and computes BM / 2 rows x 32 weight rows.  Stage rows,
+// swizzle, fragments and K order are those of the wide tiles, so every output
+// element has the same bits.
+constexpr int kNbN = 128;                             // weight rows of a narrow tile
+static_assert(2 * kNW * kRowsPerLoad == kNbN, "load split");
+
+// Which tiles a call runs on, from its experts' rows (the same everywhere:
+// every kernel of the call decides alike): 256 (wide), or the rows of its
+// narrow tiles.  Each form's time is modelled as the stages of its busiest
+// workgroup times the clocks of a stage with the whole chip at work: the
+// narrow forms' are the time their 16 KB of weights take from HBM (2.0 GHz,
+// 13 bytes a clock and CU), the wide form's that of its MFMAs.  Measured, us
+// (64 / 128 / 256 rows): 257 rows over 8 experts, the most 66, d = 7168, inter =
+// 2048: 174 / 146 / 194 (a ninth m-tile costs a second round); 61 rows over 16
+// experts, d = 2048, inter = 768: 39 / 41 / 59; 8 experts of 256 rows, d = 2048,
+// inter = 1408: 77 / 70 / 75; of 400: 119 / 98 / 73.  Over six layer shapes and
+// 16 to 512 rows an expert the rule is within 4 % of the best form but for one
+// or four experts of 200 to 512 rows (up to 13 %).  One expert of 800 or more
+// rows (shared experts) would run up to a third faster on narrow tiles alone,
+// but on the whole chip: beside the routed experts, where a step runs it, it
+// costs more than the 64 to 88 workgroups of the wide form, so kNarrowMaxRows
+// keeps it there.
+constexpr int kNarrowMaxRows = 512;
+constexpr int kWideClk = 2400, kNarrow64Clk = 1200, kNarrow128Clk = 1300;
+
+// The schedule of a call's m-tiles, built by wave 0 in registers: row bounds of
+// every expert, m-tiles before it (mt_prefix[0..E_loc]) for the chosen tile
+// rows, which are returned.  cus > 0: narrow tiles are allowed.
+__device__ __forceinline__ int build_call(const int32_t* row_offsets, int E_loc, int max_rows, int d, int inter, int cus,
+                                          int* mt_prefix, int* row_begin, int* row_end) {
+    __shared__ int tile_rows;
+    if (threadIdx.x < kWave) {
+        const int lane = threadIdx.x;
+        const int base = row_offsets[0];
+        constexpr int kPer = kMaxExpertsLocal / kWave;           // experts per lane: l = c * 64 + lane
+        int n[kPer];
+        int t64 = 0, t128 = 0, t256 = 0, most = 0;
+#pragma unroll
+        for (int c = 0; c < kPer; ++c) {
+            n[c] = 0;
+            const int l = c * kWave + lane;
+            if (c * kWave < E_loc) {                             // wave-uniform
+                int b = row_offsets[min(l, E_loc)] - base, e = row_offsets[min(l + 1, E_loc)] - base;
+                b = max(0, min(b, max_rows));
+                e = max(b, min(e, max_rows));
+                if (l < E_loc) {
+                    row_begin[l] = b;
+                    row_end[l] = e;
+                    n[c] = e - b;
+                }
+            }
+            t64 += (n[c] + 63) / 64;
+            t128 += (n[c] + 127) / 128;
+            t256 += (n[c] + 255) / 256;
+            most = max(most, n[c]);
+        }
+        int rows = kBM;
+        if (cus > 0) {
+#pragma unroll
+            for (int o = 32; o; o >>= 1) {
+                t64 += __shfl_xor(t64, o);
+                t128 += __shfl_xor(t128, o);
+                t256 += __shfl_xor(t256, o);
+                most = max(most, __shfl_xor(most, o));
+            }
+            // a workgroup's stages: its share of both GEMMs' tiles, rounded up
+            // (in floats: an integer division costs as much as the rest)
+            const float per_cu = __builtin_amdgcn_rcpf(static_cast<float>(cus));
+            auto stages = [&](int m_tiles, int n_gu, int n_dn) {
+                const float m = static_cast<float>(m_tiles) * per_cu;
+                return ceilf(m * static_cast<float>(n_gu) - 1e-3f) * static_cast<float>(d / kStageK) +
+                       ceilf(m * static_cast<float>(n_dn) - 1e-3f) * static_cast<float>(inter / kStageK);
+            };
+            if (most <= kNarrowMaxRows) {
+                const float wide = stages(t256, inter / (kBN / 2), d / kBN) * kWideClk;
+                const float n64 = stages(t64, inter / (kNbN / 2), d / kNbN) * kNarrow64Clk;
+                const float n128 = stages(t128, inter / (kNbN / 2), d / kNbN) * kNarrow128Clk;
+                if (min(n64, n128) < wide) rows = n64 <= n128 ? 64 : 128;
+            }
+        }
+        int before = 0;                                          // m-tiles of the experts before this chunk
+#pragma unroll
+        for (int c = 0; c < kPer; ++c) {
+            if (c * kWave >= E_loc) break;
+            int v = (n[c] + rows - 1) / rows;
+#pragma unroll
+            for (int o = 1; o < kWave; o <<= 1) {
+                const int u = __shfl_up(v, o);
+                if (lane >= o) v += u;
+            }
+            v += before;
+            if (c * kWave + lane < E_loc) mt_prefix[c * kWave + lane + 1] = v;
+            before = __shfl(v, kWave - 1);
+        }
+        if (lane == 0) {
+            mt_prefix[0] = 0;
+            tile_rows = rows;
+        }
+    }
+    __syncthreads();
+    return __builtin_amdgcn_readfirstlane(tile_rows);
+}
+
+// One GEMM of a call on narrow tiles.  mt_prefix, row_begin, row_end: the
+// schedule of BM-row m-tiles.  Tile order: expert, n-tile, m-tile (the m-tiles
+// that share weight rows are neighbours, on one XCD).
+template <int BM, bool GATEUP, bool GATHER>
+__device__ __forceinline__ void narrow_gemm(const uint16_t* __restrict__ A, const uint16_t* __restrict__ B0,
+                                            const uint16_t* __restrict__ B1, uint16_t* __restrict__ C,
+                                            const int* mt_prefix, const int* row_begin, const int* row_end, int E_loc,
+                                            int K, int N_out, const int32_t* __restrict__ row_src, int x_rows,
+                                            const CombinePlan& cp, const uint8_t* lds) {
+    constexpr int MB = BM / 32;                           // 16-row blocks of a wave: block i is rows (2 i + wm) * 16 ..
+    constexpr int A_LD = BM / (kNW * kRowsPerLoad), LOADS = A_LD + 2;   // loads per wave and stage
+    constexpr int STAGE_B = (BM + kNbN) * kRowB;
+    constexpr int RING = kStages * kStageBytes / STAGE_B;
+    static_assert(BM == 64 || BM == 128, "built forms");
+    const int n_tiles = GATEUP ? N_out / (kNbN / 2) : N_out / kNbN;
+    const int total = mt_prefix[E_loc] * n_tiles;
+    const int G = worker_count(total);
+    int tile = worker_id(G);
+    if (tile < 0 || tile >= total) return;
+    const int KT = K / kStageK;
+    const uint32_t pitch = static_cast<uint32_t>(K) * 2u;
+    const int lane = threadIdx.x % kWave;
+    const int wave = static_cast<int>(__builtin_amdgcn_readfirstlane(threadIdx.x / kWave));
+    const int wm = wave >> 2, wn = wave & 3;
+    const LaneMap lm = lane_map(lane);
+    const uint32_t lds_base = static_cast<uint32_t>(reinterpret_cast<uintptr_t>((lds_void*)lds));
+
+    struct Tile { int l, row0, rows, nt; };
+    auto decode = [&](int t) __attribute__((always_inline)) {
+        const int l = __builtin_amdgcn_readfirstlane(find_expert(mt_prefix, E_loc, t / n_tiles));
+        const int m0 = __builtin_amdgcn_readfirstlane(mt_prefix[l]);
+        const int cnt = __builtin_amdgcn_readfirstlane(mt_prefix[l + 1]) - m0;
+        const int u = t - m0 * n_tiles;
+        Tile T;
+        T.l = l;
+        T.nt = u / cnt;
+        T.row0 = __builtin_amdgcn_readfirstlane(row_begin[l]) + (u - T.nt * cnt) * BM;
+        T.rows = min(BM, __builtin_amdgcn_readfirstlane(row_end[l]) - T.row0);
+        return T;
+    };
+
+    // The load cursor: the next stage to issue, up to four ahead of the one
+    // computed.  A: rows 64 i + 8 wave .. + 7 of the tile (past its valid rows:
+    // the last again).  B: tile rows 32 w .. + 15 are W1 rows (or W2 rows) and
+    // 32 w + 16 .. + 31 W3 rows (W2 rows) of the output columns 16 w .. (32 w
+    // ..) of wave column w; wave 2 w + h loads the 16 rows of half h.
+    const char *pa, *pb;
+    uint32_t a_off[A_LD];
+    const uint32_t b_off0 = lm.ld_row * pitch + lm.col_b[0], b_off1 = (kRowsPerLoad + lm.ld_row) * pitch + lm.col_b[1];
+    int it_tile = tile, it_kt = 0, it_buf = 0;
+    auto cursor_tile = [&]() __attribute__((always_inline)) {
+        const Tile T = decode(it_tile);
+        pa = reinterpret_cast<const char*>(GATHER ? A : A + static_cast<size_t>(T.row0) * K);
+#pragma unroll
+        for (int j = 0; j < A_LD; ++j) {
+            const int r0 = j * kNW * kRowsPerLoad + kRowsPerLoad * wave;
+            uint32_t r = 0;
+            if (GATHER) {
+                // the eight rows through scalar loads: a vector load's wait
+                // would drain the direct loads in flight
+#pragma unroll
+                for (int i = 0; i < kRowsPerLoad; ++i) {
+                    const int v = row_src[T.row0 + min(r0 + i, T.rows - 1)];
+                    r = lm.ld_row == i ? static_cast<uint32_t>(min(max(v, 0), x_rows - 1)) : r;
+                }
+            } else {
+                r = min(r0 + lm.ld_row, T.rows - 1);
+            }
+            a_off[j] = r * pitch + ((wave & 1) ? lm.col_b[1] : lm.col_b[0]);
+        }
+        const int h = wave & 1;
+        if (GATEUP)
+            pb = reinterpret_cast<const char*>((h ? B1 : B0) + (static_cast<size_t>(T.l) * N_out + T.nt * (kNbN / 2) +
+                                                                (wave >> 1) * 16) * K);
+        else
+            pb = reinterpret_cast<const char*>(B0 + (static_cast<size_t>(T.l) * N_out + T.nt * kNbN + wave * 16) * K);
+    };
+    auto issue = [&]() __attribute__((always_inline)) {
+        const uint32_t st = lds_base + it_buf * STAGE_B;
+        lds_dma16(pa, a_off[0], st + wave * 1024);
+        if constexpr (A_LD > 1) lds_dma16(pa, a_off[A_LD - 1], st + 64 * kRowB + wave * 1024);
+        lds_dma16(pb, b_off0, st + BM * kRowB + wave * 2048);
+        lds_dma16(pb, b_off1, st + BM * kRowB + wave * 2048 + 1024);
+        it_buf = it_buf + 1 == RING ? 0 : it_buf + 1;
+        if (++it_kt < KT) {
+            pa += kRowB;
+            pb += kRowB;
+        } else if (it_tile + G < total) {
+            it_tile += G;
+            it_kt = 0;
+            cursor_tile();
+        } else {
+            it_kt = KT - 1;            // past the end: the last stage again, so that the counts of loads in flight hold
+        }
+    };
+
+    cursor_tile();
+#pragma unroll 1
+    for (int i = 0; i < RING - 1; ++i) issue();
+    int buf = 0;
+    const int pc0 = (lm.fr_kc ^ lm.fr_swz) << 4, pc1 = pc0 ^ 64;
+    for (; tile < total; tile += G) {
+        const Tile T = decode(tile);
+        const int blocks = min(MB, (T.rows - wm * 16 + 31) / 32);     // blocks with valid rows (wave-uniform)
+        f32x4 acc[MB][2];
+#pragma unroll
+        for (int i = 0; i < MB; ++i)
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) acc[i][j][r] = 0.0f;
+        for (int kt = 0; kt < KT; ++kt) {
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");       // this wave has read the stage before
+            wait_vm<(RING - 2) * LOADS>();                           // its part of this stage has landed
+            block_barrier();
+            issue();                                                 // into the buffer of the stage before
+            const uint8_t* st = lds + buf * STAGE_B;
+            const uint8_t* la = st + (wm * 16 + lm.fr_row) * kRowB;
+            const uint8_t* lb = st + (BM + wn * 32 + lm.fr_row) * kRowB;
+            bf16x8 b[2][2], a[MB][2];
+            if (blocks > 0) {
+#pragma unroll
+                for (int ks = 0; ks < 2; ++ks) {
+                    b[0][ks] = frag_at(lb + (ks ? pc1 : pc0));
+                    b[1][ks] = frag_at(lb + 16 * kRowB + (ks ? pc1 : pc0));
+                }
+            }
+#pragma unroll
+            for (int i = 0; i < MB; ++i) {
+                if (i >= blocks) break;
+#pragma unroll
+                for (int ks = 0; ks < 2; ++ks) a[i][ks] = frag_at(la + i * 32 * kRowB + (ks ? pc1 : pc0));
+            }
+#pragma unroll
+            for (int i = 0; i < MB; ++i) {
+                if (i >= blocks) break;
+#pragma unroll
+                for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+                    for (int j = 0; j < 2; ++j)
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b[j][ks], a[i][ks], acc[i][j], 0, 0, 0);
+            }
+            buf = buf + 1 == RING ? 0 : buf + 1;
+        }
+        // lane (r, q) holds columns 4 q .. + 3 of row r of each 16 x 16 block
+        const int q = lane >> 4;
+#pragma unroll
+        for (int i = 0; i < MB; ++i) {
+            const int r = (2 * i + wm) * 16 + lm.fr_row;
+            if (r >= T.rows) continue;
+            const size_t grow = static_cast<size_t>(T.row0 + r);
+            if constexpr (GATEUP) {
+                float h[4];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) h[e] = silu(acc[i][0][e]) * acc[i][1][e];
+                u32x2 o;
+                o[0] = pack_bf16x2_rne(h[0], h[1]);
+                o[1] = pack_bf16x2_rne(h[2], h[3]);
+                *reinterpret_cast<u32x2*>(C + grow * N_out + T.nt * (kNbN / 2) + wn * 16 + 4 * q) = o;
+            } else {
+                uint16_t* crow = C + grow * N_out;
+                int dst = -1;
+                float dw = 0.0f;
+                if (cp.dst) {
+                    dst = cp.dst[grow];
+                    dw = cp.w[grow];
+                    if (static_cast<unsigned>(dst) >= static_cast<unsigned>(cp.parts_rows)) dst = -1;
+                    else crow = cp.parts + static_cast<size_t>(dst) * N_out;
+                }
+#pragma unroll
+                for (int j = 0; j < 2; ++j) {
+                    u32x2 o;
+                    o[0] = pack_bf16x2_rne(acc[i][j][0], acc[i][j][1]);
+                    o[1] = pack_bf16x2_rne(acc[i][j][2], acc[i][j][3]);
+                    if (dst >= 0) {
+                        o[0] = scale_pair(o[0], dw);
+                        o[1] = scale_pair(o[1], dw);
+                    }
+                    *reinterpret_cast<u32x2*>(crow + T.nt * kNbN + wn * 32 + j * 16 + 4 * q) = o;
+                }
+            }
+        }
+    }
+    wait_vm<0>();
+}
+
 // ------------------------------------------------------------------ two-kernel bf16 path
 // One persistent kernel per GEMM (used for calls of few m-tiles).  Roles:
 // loads and stores share one in-order completion counter per wave, so a wave
@@ -645,7 +954,8 @@ template <bool GATEUP, bool GATHER>
 __global__ __launch_bounds__(kNW * kWave, 1) void ffn_gemm_bf16_kernel(
     const uint16_t* __restrict__ A, const uint16_t* __restrict__ B0, const uint16_t* __restrict__ B1,
     uint16_t* __restrict__ C, const int32_t* __restrict__ row_offsets, int E_loc, int max_rows, int K,
-    int N_out, const int32_t* __restrict__ row_src, int x_rows, CombinePlan cp) {
+    int N_out, const int32_t* __restrict__ row_src, int x_rows, CombinePlan cp, int cus, int* __restrict__ sync,
+    int n_sync) {
     __shared__ __attribute__((aligned(1024))) uint8_t lds[kStages * kStageBytes];
     __shared__ int plan_dst[kBM];
     __shared__ float plan_w[kBM];
@@ -653,7 +963,21 @@ __global__ __launch_bounds__(kNW * kWave, 1) void ffn_gemm_bf16_kernel(
     __shared__ int row_begin[kMaxExpertsLocal];
     __shared__ int row_end[kMaxExpertsLocal];
 
-    build_schedule<kBM>(row_offsets, E_loc, max_rows, mt_prefix, row_begin, row_end);
+    if (sync && blockIdx.x == 0)
+        for (int i = threadIdx.x; i < n_sync; i += blockDim.x) sync[i] = 0;
+    const int bm = build_call(row_offsets, E_loc, max_rows, GATEUP ? K : N_out, GATEUP ? N_out : K, cus, mt_prefix,
+                              row_begin, row_end);
+    if (bm == 64) {
+        narrow_gemm<64, GATEUP, GATHER>(A, B0, B1, C, mt_prefix, row_begin, row_end, E_loc, K, N_out, row_src, x_rows,
+                                        cp, lds);
+        return;
+    }
+    if (bm == 128) {
+        narrow_gemm<128, GATEUP, GATHER>(A, B0, B1, C, mt_prefix, row_begin, row_end, E_loc, K, N_out, row_src, x_rows,
+                                         cp, lds);
+        return;
+    }
+    if (sync) return;
     const int n_tiles = GATEUP ? N_out / (kBN / 2) : N_out / kBN;
     const int total = mt_prefix[E_loc] * n_tiles;
     const int KT = K / kStageK;
@@ -702,7 +1026,9 @@ __global__ __launch_bounds__(kNW * kWave, 1) void ffn_gemm_bf16_kernel(
         load_half1(ld, b_lds, 0);
     };
 
-    int tile = worker_id();
+    const int G = worker_count(total);
+    int tile = worker_id(G);
+    if (tile < 0) return;
     if (tile < total) start_tile(tile);
     while (tile < total) {
         f32x4 acc[kMI][kNJ];
@@ -714,7 +1040,7 @@ __global__ __launch_bounds__(kNW * kWave, 1) void ffn_gemm_bf16_kernel(
                 for (int r = 0; r < 4; ++r) acc[i][j][r] = 0.0f;
 
         const int cur_row0 = row0, cur_rows = rows, cur_nt = nt;
-        const int next = tile + gridDim.x;
+        const int next = tile + G;
         // in the last stage buffer 0 is free: the next tile's stage 0 lands
         // during the rest of that stage and the epilogue
         auto load_hook = [&](auto step) {
@@ -793,7 +1119,7 @@ __global__ __launch_bounds__(kNW * kWave, 1) void ffn_fused_bf16_kernel(
     const uint16_t* __restrict__ W2, uint16_t* __restrict__ H, uint16_t* __restrict__ Y,
     const int32_t* __restrict__ row_offsets, int E_loc, int max_rows, int d, int inter,
     const int32_t* __restrict__ row_src, int x_rows, int n_xcc, int* __restrict__ sync,
-    int* __restrict__ wait_err, int spin_limit, int target_bias, CombinePlan cp) {
+    int* __restrict__ wait_err, int spin_limit, int target_bias, CombinePlan cp, int cus) {
     __shared__ __attribute__((aligned(1024))) uint8_t lds[kStages * kStageBytes];
     __shared__ int plan_dst[kBM];
     __shared__ float plan_w[kBM];
@@ -804,7 +1130,17 @@ __global__ __launch_bounds__(kNW * kWave, 1) void ffn_fused_bf16_kernel(
     // barrier and read after it, and not written again before another barrier
     __shared__ int bcast[4];                // next entry; may it start early; finished count; untouched queue
 
-    build_schedule<kBM>(row_offsets, E_loc, max_rows, mt_prefix, row_begin, row_end);
+    const int bm = build_call(row_offsets, E_loc, max_rows, d, inter, cus, mt_prefix, row_begin, row_end);
+    if (bm == 64) {
+        narrow_gemm<64, false, false>(H, W2, nullptr, Y, mt_prefix, row_begin, row_end, E_loc, inter, d, nullptr, 0, cp,
+                                      lds);
+        return;
+    }
+    if (bm == 128) {
+        narrow_gemm<128, false, false>(H, W2, nullptr, Y, mt_prefix, row_begin, row_end, E_loc, inter, d, nullptr, 0,
+                                       cp, lds);
+        return;
+    }
     const int MT = mt_prefix[E_loc];
     const int n_gu = inter / (kBN / 2), n_dn = d / kBN;
     const int target = n_gu * (kNW - kNL) + target_bias;
@@ -1025,12 +1361,6 @@ __global__ __launch_bounds__(kNW * kWave, 1) void ffn_fused_bf16_kernel(
     }
 }
 
-// Zeroes the fused kernel's counters (a kernel rather than a memset, so that
-// captured graphs hold no memset node).
-__global__ __launch_bounds__(256) void zero_ints_kernel(int* __restrict__ p, int n) {
-    for (int i = threadIdx.x; i < n; i += blockDim.x) p[i] = 0;
-}
-
 // ------------------------------------------------------------------ fp32 SIMT GEMM (small shapes)
 constexpr int kF32Tile = 64;
 constexpr int kF32K = 16;
@@ -1160,11 +1490,25 @@ cap_status expert_ffn_launch(cap_dtype dt, int E_loc, int d, int inter, int max_
         // are 0..7 (one per XCD); with one XCC all CUs share one L2.  Other
         // partitions take the two-kernel path, which needs no such mapping.
         const int n_xcc = device_xcc_count();
+        // narrow tiles are for calls without the options that drive the fused
+        // kernel's grid and waits (0: not allowed)
+        const int cus = opt && (opt->max_workgroups > 0 || opt->force_wait_timeout) ? 0 : device_cu_count();
+        auto gate_up = [&](int g, int* sync, int n_sync) {
+            if (row_src)
+                ffn_gemm_bf16_kernel<true, true><<<g, kNW * kWave, 0, st>>>(
+                    a, b1, b3, h, row_offsets, E_loc, max_rows, d, inter, row_src, x_rows, none, cus, sync, n_sync);
+            else
+                ffn_gemm_bf16_kernel<true, false><<<g, kNW * kWave, 0, st>>>(
+                    a, b1, b3, h, row_offsets, E_loc, max_rows, d, inter, nullptr, 0, none, cus, sync, n_sync);
+        };
         if (max_rows >= kFusedMinRows && (n_xcc == kMaxXcc || n_xcc == 1)) {
             int* sync = reinterpret_cast<int*>(static_cast<char*>(ws) + ffn_h_bytes(max_rows, inter, dt));
-            zero_ints_kernel<<<1, 256, 0, st>>>(sync, fused_sync_ints(max_rows));
-            CAP_LAUNCH_CHECK();
             int g = persistent_grid(1ll << 30);
+            // first launch: clears the counters (a kernel rather than a memset,
+            // so that captured graphs hold no memset node) and, if the call
+            // runs on narrow tiles, does its gate/up GEMM
+            gate_up(g, sync, fused_sync_ints(max_rows));
+            CAP_LAUNCH_CHECK();
             // a caller's cap on the grid (with fewer workgroups than XCDs
             // the last one runs the untouched queues)
             if (opt && opt->max_workgroups > 0 && opt->max_workgroups < g) g = opt->max_workgroups;
@@ -1174,26 +1518,21 @@ cap_status expert_ffn_launch(cap_dtype dt, int E_loc, int d, int inter, int max_
             if (row_src)
                 ffn_fused_bf16_kernel<true><<<g, kNW * kWave, 0, st>>>(a, b1, b3, b2, h, out, row_offsets, E_loc,
                                                                        max_rows, d, inter, row_src, x_rows, n_xcc, sync,
-                                                                       err, spin, bias, cp);
+                                                                       err, spin, bias, cp, cus);
             else
                 ffn_fused_bf16_kernel<false><<<g, kNW * kWave, 0, st>>>(a, b1, b3, b2, h, out, row_offsets, E_loc,
                                                                         max_rows, d, inter, nullptr, 0, n_xcc, sync,
-                                                                        err, spin, bias, cp);
+                                                                        err, spin, bias, cp, cus);
             CAP_LAUNCH_CHECK();
             return CAP_OK;
         }
-        const long long mt_upper = (static_cast<long long>(max_rows) + kBM - 1) / kBM + E_loc;
-        const int g1 = persistent_grid(mt_upper * (inter / (kBN / 2)));
-        if (row_src)
-            ffn_gemm_bf16_kernel<true, true><<<g1, kNW * kWave, 0, st>>>(a, b1, b3, h, row_offsets, E_loc, max_rows, d,
-                                                                         inter, row_src, x_rows, none);
-        else
-            ffn_gemm_bf16_kernel<true, false><<<g1, kNW * kWave, 0, st>>>(a, b1, b3, h, row_offsets, E_loc, max_rows, d,
-                                                                          inter, nullptr, 0, none);
+        const long long mt_upper = (static_cast<long long>(max_rows) + 63) / 64 + E_loc;
+        gate_up(persistent_grid(mt_upper * (inter / (kNbN / 2))), nullptr, 0);
         CAP_LAUNCH_CHECK();
-        const int g2 = persistent_grid(mt_upper * (d / kBN));
+        const int g2 = persistent_grid(mt_upper * (d / kNbN));
         ffn_gemm_bf16_kernel<false, false><<<g2, kNW * kWave, 0, st>>>(h, b2, nullptr, out, row_offsets, E_loc,
-                                                                       max_rows, inter, d, nullptr, 0, cp);
+                                                                       max_rows, inter, d, nullptr, 0, cp, cus,
+                                                                       nullptr, 0);
         CAP_LAUNCH_CHECK();
     } else {
         const long long mt_upper = (static_cast<long long>(max_rows) + kF32Tile - 1) / kF32Tile + E_loc;
