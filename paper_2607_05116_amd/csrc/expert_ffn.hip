@@ -31,7 +31,7 @@
 //     tokens with a single kept expert on the rank, scaled by their gate
 //     weight, into the receive-side buffer instead of Y (Sec. II-C local
 //     aggregation of a one-term sum).
-// fp32 path: a plain LDS-tiled FMA kernel (small shapes only).
+// fp32 path: fp32 matrix instructions straight from global memory (small shapes).
 #include "cap_device.hpp"
 
 #include <type_traits>
@@ -1361,76 +1361,154 @@ __global__ __launch_bounds__(kNW * kWave, 1) void ffn_fused_bf16_kernel(
     }
 }
 
-// ------------------------------------------------------------------ fp32 SIMT GEMM (small shapes)
-constexpr int kF32Tile = 64;
-constexpr int kF32K = 16;
+// ------------------------------------------------------------------ fp32 GEMM (small shapes)
+// One wave computes RB x 16 rows by CB x 16 output columns on fp32 matrix
+// instructions (v_mfma_f32_16x16x4_f32: fp32 products and sums), straight from
+// global memory: lane (r, g) = (lane % 16, lane / 16) loads 16 bytes of row r
+// at K = 16 j + 4 g for both operands, and element e of them feeds the e-th of
+// four MFMAs (the same K on both sides).  The loads of a batch of U such steps
+// are all issued before its first MFMA.  What bounds the small calls is the
+// latency of that chain of loads, so a batch covers K = 128 and the tiles are
+// the smallest there are (RB = CB = 1: 169 rows over 4 experts of d = 128,
+// inter = 256 take 7 + 8 us; through 64 x 64 LDS tiles with a barrier pair every
+// 16 K they took 26 + 42).  Calls with enough rows to fill the chip with larger
+// tiles read each operand less often (RB = 4, CB = 2: 1,692 rows over 2 experts
+// of d = 328, inter = 717 127 us, 273 through the LDS tiles).
+// A4: K is a multiple of 4, so every row is 16-byte aligned.
+constexpr int kF32Waves = 4;                 // waves per workgroup, a tile each
 
-template <bool GATEUP>
-__global__ __launch_bounds__(256) void ffn_gemm_f32_kernel(
+template <bool GATEUP, int RB, int CB, bool A4>
+__global__ __launch_bounds__(kF32Waves * kWave) void ffn_gemm_f32_kernel(
     const float* __restrict__ A, const float* __restrict__ B0, const float* __restrict__ B1,
     float* __restrict__ C, const int32_t* __restrict__ row_offsets, int E_loc, int max_rows, int K, int N_out,
     const int32_t* __restrict__ row_src, int x_rows) {
-    __shared__ float sa[kF32K][kF32Tile + 1];
-    __shared__ float sb0[kF32K][kF32Tile + 1];
-    __shared__ float sb1[kF32K][kF32Tile + 1];
+    constexpr int U = RB == 1 ? 8 : 2;       // K steps of 16 per batch of loads
     __shared__ int mt_prefix[kMaxExpertsLocal + 1];
     __shared__ int row_begin[kMaxExpertsLocal];
     __shared__ int row_end[kMaxExpertsLocal];
-    build_schedule<kF32Tile>(row_offsets, E_loc, max_rows, mt_prefix, row_begin, row_end);
-    const int n_tiles = (N_out + kF32Tile - 1) / kF32Tile;
-    const int total = mt_prefix[E_loc] * n_tiles;
-    const int tx = threadIdx.x % 16, ty = threadIdx.x / 16;
-    for (int tile = blockIdx.x; tile < total; tile += gridDim.x) {
-        const int m_tile = tile / n_tiles, nt = tile % n_tiles;
-        const int l = find_expert(mt_prefix, E_loc, m_tile);
-        const int row0 = row_begin[l] + (m_tile - mt_prefix[l]) * kF32Tile;
-        const int rows_valid = min(kF32Tile, row_end[l] - row0);
-        const float* W0 = B0 + static_cast<size_t>(l) * N_out * K;
-        const float* W1 = GATEUP ? B1 + static_cast<size_t>(l) * N_out * K : nullptr;
-        float acc0[4][4] = {}, acc1[4][4] = {};
-        for (int k0 = 0; k0 < K; k0 += kF32K) {
-            for (int i = threadIdx.x; i < kF32K * kF32Tile; i += 256) {
-                const int r = i / kF32K, kk = i % kF32K;
-                const int gk = k0 + kk;
-                int gr = row0 + min(r, rows_valid - 1);
-                if (row_src) gr = min(max(row_src[gr], 0), x_rows - 1);
-                const int gn = nt * kF32Tile + r;
-                sa[kk][r] = gk < K ? A[static_cast<size_t>(gr) * K + gk] : 0.0f;
-                sb0[kk][r] = (gk < K && gn < N_out) ? W0[static_cast<size_t>(gn) * K + gk] : 0.0f;
-                if (GATEUP) sb1[kk][r] = (gk < K && gn < N_out) ? W1[static_cast<size_t>(gn) * K + gk] : 0.0f;
+    build_schedule<RB * 16>(row_offsets, E_loc, max_rows, mt_prefix, row_begin, row_end);
+    const int MT = mt_prefix[E_loc];
+    const int n_tiles = (N_out + CB * 16 - 1) / (CB * 16);
+    const int lane = threadIdx.x % kWave;
+    const int r16 = lane & 15, g = lane >> 4;
+    const int wave = static_cast<int>(__builtin_amdgcn_readfirstlane(threadIdx.x / kWave));
+    // m-tile fastest: a workgroup's waves share their weight rows
+    for (int tile = blockIdx.x * kF32Waves + wave; tile < MT * n_tiles; tile += gridDim.x * kF32Waves) {
+        const int nt = tile / MT, m_tile = tile - nt * MT;
+        const int l = __builtin_amdgcn_readfirstlane(find_expert(mt_prefix, E_loc, m_tile));
+        const int row0 = __builtin_amdgcn_readfirstlane(row_begin[l] + (m_tile - mt_prefix[l]) * (RB * 16));
+        const int rows = __builtin_amdgcn_readfirstlane(row_end[l]) - row0;
+        const int col0 = nt * (CB * 16);
+        const float* pa[RB];
+        const float* pb[GATEUP ? 2 * CB : CB];        // gate blocks, then up blocks
+#pragma unroll
+        for (int i = 0; i < RB; ++i) {
+            int r = row0 + min(16 * i + r16, rows - 1);          // past the expert's end: its last row again
+            if (row_src) r = min(max(row_src[r], 0), x_rows - 1);
+            pa[i] = A + static_cast<size_t>(r) * K + 4 * g;
+        }
+#pragma unroll
+        for (int j = 0; j < CB; ++j) {
+            const size_t n = static_cast<size_t>(l) * N_out + min(col0 + 16 * j + r16, N_out - 1);
+            pb[j] = B0 + n * K + 4 * g;
+            if constexpr (GATEUP) pb[CB + j] = B1 + n * K + 4 * g;
+        }
+        constexpr int NB = GATEUP ? 2 * CB : CB;
+        // two sums per output, of the even and the odd K steps: half the chain
+        // of dependent MFMAs, and less rounding than one running sum
+        f32x4 acc[RB][NB], odd[RB][NB];
+#pragma unroll
+        for (int i = 0; i < RB; ++i)
+#pragma unroll
+            for (int j = 0; j < NB; ++j)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) acc[i][j][e] = odd[i][j][e] = 0.0f;
+        // four values of a row at K = k .. k + 3, zero past K
+        auto load4 = [&](const float* p, int k) __attribute__((always_inline)) {
+            f32x4 v = {0.0f, 0.0f, 0.0f, 0.0f};
+            if constexpr (A4) {
+                if (k + 4 * g < K) v = *reinterpret_cast<const f32x4*>(p + k);
+            } else {
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (k + 4 * g + e < K) v[e] = p[k + e];
             }
-            __syncthreads();
+            return v;
+        };
+        for (int k0 = 0; k0 < K; k0 += 16 * U) {
+            f32x4 a[U][RB], b[U][NB];
 #pragma unroll
-            for (int kk = 0; kk < kF32K; ++kk) {
-                float a[4], b0[4], b1[4];
+            for (int u = 0; u < U; ++u) {
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    a[i] = sa[kk][ty * 4 + i];
-                    b0[i] = sb0[kk][tx * 4 + i];
-                    b1[i] = GATEUP ? sb1[kk][tx * 4 + i] : 0.0f;
-                }
+                for (int i = 0; i < RB; ++i) a[u][i] = load4(pa[i], k0 + 16 * u);
 #pragma unroll
-                for (int i = 0; i < 4; ++i)
+                for (int j = 0; j < NB; ++j) b[u][j] = load4(pb[j], k0 + 16 * u);
+            }
 #pragma unroll
-                    for (int j = 0; j < 4; ++j) {
-                        acc0[i][j] = __builtin_fmaf(a[i], b0[j], acc0[i][j]);
-                        if (GATEUP) acc1[i][j] = __builtin_fmaf(a[i], b1[j], acc1[i][j]);
+            for (int ue = 0; ue < 4 * U; ++ue) {
+                const int u = ue / 8 * 2 + ue % 2, e = ue % 8 / 2;           // even and odd steps in turn
+#pragma unroll
+                for (int i = 0; i < RB; ++i)
+#pragma unroll
+                    for (int j = 0; j < NB; ++j) {
+                        f32x4& s = u % 2 ? odd[i][j] : acc[i][j];
+                        s = __builtin_amdgcn_mfma_f32_16x16x4f32(b[u][j][e], a[u][i][e], s, 0, 0, 0);
                     }
             }
-            __syncthreads();
         }
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int r = ty * 4 + i;
-            if (r >= rows_valid) continue;
+        for (int i = 0; i < RB; ++i)
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int n = nt * kF32Tile + tx * 4 + j;
-                if (n >= N_out) continue;
-                C[static_cast<size_t>(row0 + r) * N_out + n] =
-                    GATEUP ? silu(acc0[i][j]) * acc1[i][j] : acc0[i][j];
+            for (int j = 0; j < NB; ++j)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) acc[i][j][e] += odd[i][j][e];
+        // lane (r, g) holds columns 4 g .. + 3 of row r of each 16 x 16 block
+        const bool c4 = (N_out & 3) == 0;
+#pragma unroll
+        for (int i = 0; i < RB; ++i) {
+            if (16 * i + r16 >= rows) continue;
+            float* crow = C + static_cast<size_t>(row0 + 16 * i + r16) * N_out;
+#pragma unroll
+            for (int j = 0; j < CB; ++j) {
+                const int c = col0 + 16 * j + 4 * g;
+                f32x4 v;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    if constexpr (GATEUP) v[e] = silu(acc[i][j][e]) * acc[i][CB + j][e];
+                    else v[e] = acc[i][j][e];
+                }
+                if (c4) {
+                    if (c < N_out) *reinterpret_cast<f32x4*>(crow + c) = v;
+                } else {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        if (c + e < N_out) crow[c + e] = v[e];
+                }
             }
         }
+    }
+}
+
+template <bool GATEUP>
+void launch_ffn_f32(const float* a, const float* b0, const float* b1, float* c, const int32_t* row_offsets, int E_loc,
+                    int max_rows, int K, int N_out, const int32_t* row_src, int x_rows, hipStream_t st) {
+    // larger tiles from the row capacity on at which they give every SIMD a wave
+    const long long cus = device_cu_count();
+    const long long large = (max_rows / 64 + E_loc) * static_cast<long long>((N_out + 31) / 32);
+    const long long small = (max_rows / 16 + E_loc) * static_cast<long long>((N_out + 15) / 16);
+    const bool big = large >= 4 * cus;
+    const long long need = ((big ? large : small) + kF32Waves - 1) / kF32Waves;
+    const int grid = static_cast<int>(need < 8 * cus ? need : 8 * cus);
+    const bool a4 = (K & 3) == 0;
+    auto go = [&](auto kernel) {
+        kernel<<<grid, kF32Waves * kWave, 0, st>>>(a, b0, b1, c, row_offsets, E_loc, max_rows, K, N_out, row_src, x_rows);
+    };
+    if (big) {
+        if (a4) go(ffn_gemm_f32_kernel<GATEUP, 4, 2, true>);
+        else go(ffn_gemm_f32_kernel<GATEUP, 4, 2, false>);
+    } else {
+        if (a4) go(ffn_gemm_f32_kernel<GATEUP, 1, 1, true>);
+        else go(ffn_gemm_f32_kernel<GATEUP, 1, 1, false>);
     }
 }
 
@@ -1535,16 +1613,11 @@ cap_status expert_ffn_launch(cap_dtype dt, int E_loc, int d, int inter, int max_
                                                                        nullptr, 0);
         CAP_LAUNCH_CHECK();
     } else {
-        const long long mt_upper = (static_cast<long long>(max_rows) + kF32Tile - 1) / kF32Tile + E_loc;
-        const int g1 = persistent_grid(mt_upper * ((inter + kF32Tile - 1) / kF32Tile)) * 4;
-        ffn_gemm_f32_kernel<true><<<g1, 256, 0, st>>>(
-            static_cast<const float*>(xs), static_cast<const float*>(w1), static_cast<const float*>(w3),
-            static_cast<float*>(ws), row_offsets, E_loc, max_rows, d, inter, row_src, x_rows);
+        launch_ffn_f32<true>(static_cast<const float*>(xs), static_cast<const float*>(w1), static_cast<const float*>(w3),
+                             static_cast<float*>(ws), row_offsets, E_loc, max_rows, d, inter, row_src, x_rows, st);
         CAP_LAUNCH_CHECK();
-        const int g2 = persistent_grid(mt_upper * ((d + kF32Tile - 1) / kF32Tile)) * 4;
-        ffn_gemm_f32_kernel<false><<<g2, 256, 0, st>>>(
-            static_cast<const float*>(ws), static_cast<const float*>(w2), nullptr, static_cast<float*>(y),
-            row_offsets, E_loc, max_rows, inter, d, nullptr, 0);
+        launch_ffn_f32<false>(static_cast<const float*>(ws), static_cast<const float*>(w2), nullptr,
+                              static_cast<float*>(y), row_offsets, E_loc, max_rows, inter, d, nullptr, 0, st);
         CAP_LAUNCH_CHECK();
     }
     return CAP_OK;
