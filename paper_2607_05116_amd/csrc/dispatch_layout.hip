@@ -16,8 +16,8 @@
 //               chunks (in place) and the column total; one more block sums
 //               the volumes.
 //   3. scatter  one block per chunk: every block scans the column totals
-//               itself (expert offsets, receive offsets; block 0 also writes
-//               them out with the send counts and offsets), then stable
+//               itself (expert offsets, receive offsets; block 0 also writes them
+//               out, the first chunk of a rank its send counts), then stable
 //               in-chunk ranks from per-wave bitsets (LDS atomicOr, order
 //               independent) and popcounts give slot_pos, copy_row and
 //               recv_token.

@@ -272,10 +272,13 @@ __device__ __forceinline__ void block_exclusive_scan2(int a, int b, int (*wsum)[
 // load that does not depend on another is issued first, so the block waits
 // for one round of memory latency before its LDS work: the placement tables,
 // the column totals, the chunk's column bases, the token's slots and mask, and
-// in block 0 the rank-boundary bases that give send_counts (send_offsets then
-// come from one block scan over the (s, d) pairs).
-constexpr int kSendPerThread = kMaxR * kMaxR / kChunk;   // (s, d) pairs per thread in block 0
-static_assert(kMaxR * kMaxR % kChunk == 0, "send-count pairs split evenly over the block");
+// the bases at the next source rank's first chunk.  The first chunk of source
+// rank s writes row s of send_counts and send_offsets: a row is at most one
+// wave (R <= 64), whose one scan gives the offsets.  (When block 0 wrote all R
+// rows, its 16 pairs per thread and their block scan took longer than the
+// scatter of any chunk and set the launch's time: 11.0 -> 8.5 us for 32,768
+// tokens, 256 experts and 32 ranks, 7.9 -> 6.6 us for 256 tokens and 8 ranks.)
+static_assert(kMaxR <= kWave, "a row of send counts is one wave");
 
 __device__ __forceinline__ void layout_scatter_block(
     const Geom& g, const int32_t* __restrict__ idx, const uint8_t* __restrict__ keep,
@@ -290,7 +293,6 @@ __device__ __forceinline__ void layout_scatter_block(
     __shared__ int32_t gbase[kMaxW];
     __shared__ int32_t roff[kMaxR + 1];
     __shared__ int wsum[2][kWavesPerChunk];
-    __shared__ int32_t sc_lds[kMaxR * kMaxR];
     const int i = threadIdx.x;                  // E <= 256 = kChunk threads
     const int wave = i / kWave;
 
@@ -318,22 +320,9 @@ __device__ __forceinline__ void layout_scatter_block(
         }
     }
     const uint64_t m_raw = mask[tc];
-    // block 0: send_counts[s][d] = rows of column E + d from the chunks of rank
-    // s = (base at rank s + 1's first chunk, or the total) - (base at rank s's)
-    // (thread i takes the consecutive pairs q = i * kSendPerThread + j, those
-    // past R * R clamped to the last one)
-    int sc_hi[kSendPerThread], sc_lo[kSendPerThread];
-    if (bid == 0) {
-#pragma unroll
-        for (int j = 0; j < kSendPerThread; ++j) {
-            const int q = min(i * kSendPerThread + j, g.R * g.R - 1);
-            const int s = small_quotient(q, g.R), d = q - s * g.R;
-            const int32_t* lp = ws.part + static_cast<size_t>(s * g.cpr * g.sub) * g.W + g.E + d;
-            const int32_t* hp = (s + 1 < g.R) ? lp + static_cast<size_t>(g.cpr * g.sub) * g.W : ws.coltot + g.E + d;
-            sc_hi[j] = *hp;
-            sc_lo[j] = *lp;
-        }
-    }
+    // bases of the device columns past the source rank's last chunk
+    const int32_t* const end = src + 1 < g.R ? ws.part + static_cast<size_t>((src + 1) * g.cpr * g.sub) * g.W : ws.coltot;
+    const int end_d = end[g.E + ir];
 
     // ---- LDS work
 #pragma unroll
@@ -370,36 +359,20 @@ __device__ __forceinline__ void layout_scatter_block(
         if (i == 0) expert_offsets[g.E] = rows_total;
         if (i < g.R) recv_offsets[i] = doff;
         if (i == 0) recv_offsets[g.R] = recv_total;
-        // send_offsets[s][d] = sum of send_counts[s][d'] over d' < d: the
-        // exclusive scan over all pairs in row-major order, less its value at
-        // the row's first pair
-        const int nq = g.R * g.R;
-        int sc[kSendPerThread];
+    }
+    // send_counts[src][d] = rows of column E + d from the rank's chunks, and
+    // send_offsets[src][d] = their sum over d' < d
+    if (wave == 0 && bid == src * g.cpr) {
+        const int n = i < g.R ? end_d - cb_d : 0;
+        int inc = n;
 #pragma unroll
-        for (int j = 0; j < kSendPerThread; ++j) sc[j] = sc_hi[j] - sc_lo[j];
-        int local[kSendPerThread];
-        int mine = 0;
-#pragma unroll
-        for (int j = 0; j < kSendPerThread; ++j) {
-            local[j] = mine;
-            mine += (i * kSendPerThread + j < nq) ? sc[j] : 0;
+        for (int off = 1; off < kMaxR; off <<= 1) {
+            const int u = __shfl_up(inc, off);
+            if (i >= off) inc += u;
         }
-        int all;
-        const int base = block_exclusive_scan(mine, wsum[0], &all);
-#pragma unroll
-        for (int j = 0; j < kSendPerThread; ++j) {
-            const int q = i * kSendPerThread + j;
-            if (q < nq) sc_lds[q] = base + local[j];
-        }
-        __syncthreads();
-#pragma unroll
-        for (int j = 0; j < kSendPerThread; ++j) {
-            const int q = i * kSendPerThread + j;
-            if (q < nq) {
-                const int row0 = q - (q - small_quotient(q, g.R) * g.R);   // s * R
-                send_counts[q] = sc[j];
-                send_offsets[q] = base + local[j] - sc_lds[row0];
-            }
+        if (i < g.R) {
+            send_counts[src * g.R + i] = n;
+            send_offsets[src * g.R + i] = inc - n;
         }
     }
     __syncthreads();
