@@ -17,6 +17,7 @@ constexpr int kMaxW = kMaxE + kMaxR;
 // of the workspace), each counting a consecutive part of the chunk.
 struct Geom {
     int T, E, k, R, rpn, tpr, E_loc, cpr, C, W, sub, Cs;
+    int kinv;   // ceil(2^16 / k): (n * kinv) >> 16 is n / k for n <= kChunk * kMaxK
 };
 
 struct Workspace {
@@ -233,7 +234,7 @@ __global__ __launch_bounds__(kChunk) void layout_colscan_kernel(Geom g, Workspac
 
 // ---------------------------------------------------------------- 3. scatter
 // Exclusive scans of two values over the 256 threads of a block in one pass;
-// *total_a / *total_b get the sums.
+// *total_a / *total_b get the sums.  wsum is not free before the next barrier.
 __device__ __forceinline__ void block_exclusive_scan2(int a, int b, int (*wsum)[kWavesPerChunk], int& ea, int& eb,
                                                       int* total_a, int* total_b) {
     const int lane = lane_id(), wave = threadIdx.x / kWave;
@@ -261,7 +262,6 @@ __device__ __forceinline__ void block_exclusive_scan2(int a, int b, int (*wsum)[
         all_a += wsum[0][w];
         all_b += wsum[1][w];
     }
-    __syncthreads();
     *total_a = all_a;
     *total_b = all_b;
     ea = before_a + ia - a;
@@ -278,6 +278,14 @@ __device__ __forceinline__ void block_exclusive_scan2(int a, int b, int (*wsum)[
 // rows, its 16 pairs per thread and their block scan took longer than the
 // scatter of any chunk and set the launch's time: 11.0 -> 8.5 us for 32,768
 // tokens, 256 experts and 32 ranks, 7.9 -> 6.6 us for 256 tokens and 8 ranks.)
+// The chunk's (token, slot) pairs go to the threads in their memory order, so
+// slot loads and stores are whole lines (a token per thread touched 16 lines
+// an instruction) and a chunk of few tokens takes fewer than k turns: 6.6 ->
+// 4.9 us for 256 tokens of 8 slots over 8 ranks (8.5 -> 8.4 us for the 32,768
+// tokens, where the co-activation reduce of the same launch takes as long).
+// One token per thread with the lookups of all its slots in one branch-free
+// batch was slower there (9.5 us): the block runs its code once, so its
+// length counts.
 static_assert(kMaxR <= kWave, "a row of send counts is one wave");
 
 __device__ __forceinline__ void layout_scatter_block(
@@ -298,7 +306,8 @@ __device__ __forceinline__ void layout_scatter_block(
 
     // ---- one round of independent loads (indices clamped rather than tested,
     // so that no branch splits the loads and they all go out before the first
-    // wait; what a clamped lane loaded is dropped after the wait)
+    // wait; what a clamped lane loaded is dropped after the wait); turns past the
+    // chunk's last pair are skipped by the whole block
     const int32_t* cb = ws.part + static_cast<size_t>(bid) * g.sub * g.W;     // the chunk's first partial row
     const int ie = min(i, g.E - 1), ir = min(i, g.R - 1);
     int er_i = er[ie], el_i = el[ie], tot_e = ws.coltot[ie], cb_e = cb[ie];
@@ -308,15 +317,18 @@ __device__ __forceinline__ void layout_scatter_block(
     const int t = t0 + i;
     const bool live = t < t1;
     const int tc = min(t, t1 - 1);              // chunks are never empty
+    const int pairs = (t1 - t0) * g.k;
+    const size_t q0 = static_cast<size_t>(t0) * g.k;
     int e_raw[kMaxK];
     uint8_t kp_raw[kMaxK];
-    {
-        const size_t q0 = static_cast<size_t>(tc) * g.k;
 #pragma unroll
-        for (int s = 0; s < kMaxK; ++s) {
-            const size_t q = q0 + min(s, g.k - 1);
-            e_raw[s] = idx[q];
-            kp_raw[s] = keep[q];
+    for (int j = 0; j < kMaxK; ++j) {
+        e_raw[j] = -1;
+        kp_raw[j] = 0;
+        if (j * kChunk < pairs) {
+            const size_t q = q0 + min(i + j * kChunk, pairs - 1);
+            e_raw[j] = idx[q];
+            kp_raw[j] = keep[q];
         }
     }
     const uint64_t m_raw = mask[tc];
@@ -330,17 +342,11 @@ __device__ __forceinline__ void layout_scatter_block(
         for (int c = i; c < g.W; c += kChunk) bits[w][c] = 0ull;
     if (i >= g.E) tot_e = 0;
     if (i >= g.R) tot_d = 0;
-#pragma unroll
-    for (int s = 0; s < kMaxK; ++s)
-        if (!live || s >= g.k) {
-            e_raw[s] = -1;
-            kp_raw[s] = 0;
-        }
     const uint64_t m = live ? device_bits(m_raw, g.R) : 0ull;
     if (i < g.E) {
         const bool ok = (static_cast<unsigned>(er_i) < static_cast<unsigned>(g.R)) &
                         (static_cast<unsigned>(el_i) < static_cast<unsigned>(g.E_loc));
-        pos_lds[i] = ok ? er_i * g.E_loc + el_i : -1;
+        pos_lds[i] = ok ? (er_i << 16) | (er_i * g.E_loc + el_i) : -1;   // device, slot position
     }
     // expert offsets (slot-position order) and receive offsets from the column totals
     int eoff, doff, rows_total, recv_total;
@@ -377,49 +383,51 @@ __device__ __forceinline__ void layout_scatter_block(
     }
     __syncthreads();
 
-    const unsigned long long me = 1ull << lane_id();
     int P[kMaxK];
 #pragma unroll
-    for (int s = 0; s < kMaxK; ++s)
-        P[s] = (kp_raw[s] && static_cast<unsigned>(e_raw[s]) < static_cast<unsigned>(g.E)) ? pos_lds[e_raw[s]] : -1;
-    if (live) {
-#pragma unroll
-        for (int s = 0; s < kMaxK; ++s)
-            if (P[s] >= 0) atomicOr(&bits[wave][P[s]], me);
-        for (uint64_t b = m; b; b &= b - 1)
-            atomicOr(&bits[wave][g.E + __ffsll(static_cast<unsigned long long>(b)) - 1], me);
+    for (int j = 0; j < kMaxK; ++j) {
+        P[j] = -1;
+        const int n = i + j * kChunk;
+        if (j * kChunk >= pairs) continue;
+        if (n < pairs && kp_raw[j] && static_cast<unsigned>(e_raw[j]) < static_cast<unsigned>(g.E)) P[j] = pos_lds[e_raw[j]];
+        const int tok = (n * g.kinv) >> 16;
+        if (P[j] >= 0) atomicOr(&bits[tok / kWave][P[j] & 0xFFFF], 1ull << (tok % kWave));
     }
+    for (uint64_t b = m; b; b &= b - 1)
+        atomicOr(&bits[wave][g.E + __ffsll(static_cast<unsigned long long>(b)) - 1], 1ull << lane_id());
     __syncthreads();
     for (int col = threadIdx.x; col < g.W; col += kChunk) {
-        int run = 0;
+        int run = gbase[col];
 #pragma unroll
         for (int w = 0; w < kWavesPerChunk; ++w) {
-            pre[w][col] = run;
+            pre[w][col] = run;                  // the column's rows before wave w's tokens
             run += __popcll(bits[w][col]);
         }
     }
     __syncthreads();
-    if (!live) return;
-    const unsigned long long below = lanemask_lt();
 #pragma unroll
-    for (int s = 0; s < kMaxK; ++s) {
-        if (s >= g.k) break;
-        const size_t q = static_cast<size_t>(t) * g.k + s;
+    for (int j = 0; j < kMaxK; ++j) {
+        const int n = i + j * kChunk;
+        if (j * kChunk >= pairs) break;
+        const int tok = (n * g.kinv) >> 16, w = tok / kWave;
+        const unsigned long long at = 1ull << (tok % kWave);
         int sp = -1, cr = -1;
-        if (P[s] >= 0) {
-            const int Pe = P[s];
-            sp = gbase[Pe] + pre[wave][Pe] + __popcll(bits[wave][Pe] & below);
-            const int d = small_quotient(Pe, g.E_loc);
-            const int col = g.E + d;
-            if ((m >> d) & 1ull) cr = gbase[col] + pre[wave][col] + __popcll(bits[wave][col] & below);
+        if (P[j] >= 0) {
+            const int ce = P[j] & 0xFFFF, cd = g.E + (P[j] >> 16);
+            const unsigned long long be = bits[w][ce], bd = bits[w][cd];
+            sp = pre[w][ce] + __popcll(be & (at - 1));
+            if (bd & at) cr = pre[w][cd] + __popcll(bd & (at - 1));   // the mask holds the device
         }
-        slot_pos[q] = sp;
-        copy_row[q] = cr;
+        if (n < pairs) {
+            slot_pos[q0 + n] = sp;
+            copy_row[q0 + n] = cr;
+        }
     }
+    const unsigned long long below = lanemask_lt();
     for (uint64_t b = m; b; b &= b - 1) {
         const int d = __ffsll(static_cast<unsigned long long>(b)) - 1;
         const int col = g.E + d;
-        const int row = gbase[col] + pre[wave][col] + __popcll(bits[wave][col] & below);
+        const int row = pre[wave][col] + __popcll(bits[wave][col] & below);
         const long long at = static_cast<long long>(roff[d]) + row;
         if (at >= 0 && at < static_cast<long long>(g.T) * g.k) recv_token[at] = t;   // malformed masks stay in bounds
     }
@@ -445,6 +453,7 @@ inline Geom make_geom(const cap_topology* tp, int sub) {
     g.W = g.E + g.R;
     g.sub = sub;
     g.Cs = g.C * sub;
+    g.kinv = (65536 + g.k - 1) / g.k;
     return g;
 }
 
