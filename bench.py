@@ -550,7 +550,7 @@ def main():
                        + ", rank 0: one fused gate/up + down launch reading x rows in place"
                        + (" and writing single-expert tokens' weighted rows into the receive buffer"
                           if L.fused_combine else "")
-                       + " (the call's events also hold its one-block counter clear, a few us)"),
+                       + " (the call's events also hold the launch before it that clears its counters, a few us)"),
             "bound": "mfma", "achieved": achieved, "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s",
             "frac": achieved / PEAK_BF16_TFLOPS, "traffic": traffic,
             "flops_per_call": flops, "rows": rows, "avg_call_ms": ffn_ms,
