@@ -223,7 +223,9 @@ __device__ __forceinline__ const bf16x8& frag_at(const uint8_t* p) { return *rei
 
 // Loads of one tile for one loader wave.  A: rows wave * 64 .. + 63, 8 loads a
 // stage (lane l of load i: byte offset a_off[i] from the operand base: a tile
-// row, clamped to the expert's last, or a gathered row of x).  B: of quarter q
+// row, clamped to the expert's last, or a gathered row of x), none of them by
+// a loader whose own wave computes nothing (a_on: wave row w / 2 has rows; the
+// rows 64 w .. it loads come after those).  B: of quarter q
 // (rows wn * 128 + 32 q .. + 31 of both wave columns wn) the 16 rows wn =
 // wave / 2, 16 (wave % 2) ..: 2 loads a quarter.  The pointers run along K:
 // a and b0 / b1 (quarters 0, 1) one stage ahead of c0 / c1 (quarters 2, 3).
@@ -231,6 +233,7 @@ struct Loads {
     const char *a, *b0, *b1, *c0, *c1;
     uint32_t a_off[kALd];
     uint32_t b_off[2];
+    bool a_on;
 };
 
 template <int I>
@@ -246,8 +249,8 @@ __device__ __forceinline__ void load_b(const Loads& s, uint32_t b_lds, int buf) 
 }
 __device__ __forceinline__ void step_half0(Loads& s) { s.a += kRowB; s.b0 += kRowB; s.b1 += kRowB; }
 __device__ __forceinline__ void step_half1(Loads& s) { s.c0 += kRowB; s.c1 += kRowB; }
-__device__ __forceinline__ void load_half0(Loads& s, uint32_t a_lds, uint32_t b_lds, int buf) {
-    static_for<kALd>([&](auto I) { load_a<I.value>(s, a_lds, buf); });
+__device__ __forceinline__ void load_half0(Loads& s, bool a_on, uint32_t a_lds, uint32_t b_lds, int buf) {
+    if (a_on) static_for<kALd>([&](auto I) { load_a<I.value>(s, a_lds, buf); });
     static_for<4>([&](auto I) { load_b<0, I.value>(s, b_lds, buf); });
     step_half0(s);
 }
@@ -291,8 +294,12 @@ __device__ __forceinline__ void load_half1(Loads& s, uint32_t b_lds, int buf) {
 // 393 -> 358 us, 3,001 rows of d = 2048, inter = 1408 98 -> 89 us.  Issuing
 // twelve of a stage's sixteen loads in quarters 1 and 2 was no faster, nor a
 // raised wave priority around the MFMAs or for the loaders (0 to 2 % slower).
-// A wave whose 64 rows all lie past the tile's valid rows (active =
-// false) computes nothing: its accumulators stay zero and are never stored.
+// A wave whose 64 rows all lie past the tile's valid rows (active = false)
+// computes nothing: its accumulators stay zero and are never stored.  A loader
+// among them loads no A either, and its waits count without those loads: tiles
+// of 64 rows or fewer then bring 16 KB of A a stage instead of 32.  (A third
+// form of the loop for the loaders of which only the rows they load lie past
+// the end was 1 to 4 % slower on 300 rows an expert of d = 7168.)
 template <int N>
 __device__ __forceinline__ void wait_vm() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
 
@@ -318,6 +325,8 @@ enum KStep { kMiddle, kFirst, kSecond, kLast2, kPreLast, kLast };
 template <bool LOADER, bool ACTIVE, typename Hook>
 __device__ __forceinline__ void k_loop(int KT, const uint8_t* lds, int wm, int wn, int lane, f32x4 (&acc)[kMI][kNJ], Loads& ld, uint32_t a_lds, uint32_t b_lds,
                                        Hook&& hook) {
+    constexpr bool LOAD_A = LOADER && ACTIVE;
+    constexpr int kA = LOAD_A ? kALd : 0;              // this wave's A loads of a stage
     bf16x8 a[kMI][2], b0[2][2], b1[2][2];
     const LaneMap lm = lane_map(opaque(lane));
     const int pc0 = (lm.fr_kc ^ lm.fr_swz) << 4, pc1 = pc0 ^ 64;
@@ -353,7 +362,7 @@ __device__ __forceinline__ void k_loop(int KT, const uint8_t* lds, int wm, int w
     asm volatile("s_nop 7");
     if (LOADER) wait_vm<0>();
     block_barrier();                                   // stage 0 visible; buffer 1 free
-    if (LOADER) load_half0(ld, a_lds, b_lds, 1);
+    if (LOADER) load_half0(ld, LOAD_A, a_lds, b_lds, 1);
     if constexpr (ACTIVE)
         static_for<4>([&](auto N) {
             read_b(b0, 0, 0, N);
@@ -381,7 +390,7 @@ __device__ __forceinline__ void k_loop(int KT, const uint8_t* lds, int wm, int w
         if constexpr (step == kLast) hook(std::integral_constant<KStep, kPreLast>{});
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");       // A, quarters 0 and 1 read
         if constexpr (LOADER) {                                  // quarters 2, 3 of stage kt landed
-            wait_vm<next1 ? kALd + 8 : 0>();
+            wait_vm<next1 ? kA + 8 : 0>();
         }
         block_barrier();                                         // barrier a
         if constexpr (step != kMiddle) hook(STEP);
@@ -390,7 +399,7 @@ __device__ __forceinline__ void k_loop(int KT, const uint8_t* lds, int wm, int w
                 read_b(b0, buf, 2, G);
                 mfma4(b1, N1, G);
             }
-            if constexpr (LOADER && next2) load_a<G.value>(ld, a_lds, buf);
+            if constexpr (LOAD_A && next2) load_a<G.value>(ld, a_lds, buf);
             __builtin_amdgcn_sched_barrier(0);
         });
         static_for<4>([&](auto G) {                                            // quarter 2
@@ -398,12 +407,12 @@ __device__ __forceinline__ void k_loop(int KT, const uint8_t* lds, int wm, int w
                 read_b(b1, buf, 3, G);
                 mfma4(b0, N2, G);
             }
-            if constexpr (LOADER && next2) load_a<4 + G.value>(ld, a_lds, buf);
+            if constexpr (LOAD_A && next2) load_a<4 + G.value>(ld, a_lds, buf);
             __builtin_amdgcn_sched_barrier(0);
         });
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");       // quarters 2, 3 read
         if constexpr (LOADER && next1) {                         // A, quarters 0, 1 of stage kt + 1 landed
-            wait_vm<next2 ? kALd + 4 : 4>();
+            wait_vm<next2 ? kA + 4 : 4>();
         }
         block_barrier();                                         // barrier c
         static_for<4>([&](auto G) {                                            // quarter 3
@@ -611,6 +620,7 @@ __device__ __forceinline__ void tile_loads(Loads& s, bool gu, bool gathered, con
     const LaneMap lm = lane_map(opaque(lane));
     const uint32_t pitch = static_cast<uint32_t>(K) * 2u;
     s.a = gathered ? reinterpret_cast<const char*>(A) : reinterpret_cast<const char*>(A + static_cast<size_t>(row0) * K);
+    s.a_on = lw / kWavesN * kWM < rows;
     const int wn = lw >> 1, h = lw & 1;
     if (gu) {
         const size_t row = static_cast<size_t>(l) * N_out + nt * (kBN / 2) + wn * (kWN / 2) + h * 16;
@@ -1022,7 +1032,7 @@ __global__ __launch_bounds__(kNW * kWave, 1) void ffn_gemm_bf16_kernel(
         rows = __builtin_amdgcn_readfirstlane(min(kBM, row_end[l] - row0));
         if (!loader) return;
         tile_loads(ld, GATEUP, GATHER, A, B0, B1, l, row0, rows, nt, wave, K, N_out, lane, row_src, x_rows);
-        load_half0(ld, a_lds, b_lds, 0);
+        load_half0(ld, ld.a_on, a_lds, b_lds, 0);
         load_half1(ld, b_lds, 0);
     };
 
@@ -1220,7 +1230,7 @@ __global__ __launch_bounds__(kNW * kWave, 1) void ffn_fused_bf16_kernel(
     };
     auto issue0 = [&]() {
         if (!loader) return;
-        load_half0(ld, a_lds, b_lds, 0);
+        load_half0(ld, ld.a_on, a_lds, b_lds, 0);
         load_half1(ld, b_lds, 0);
     };
     // wave 0 waits until m-tile m's H rows are complete, then the workgroup goes on

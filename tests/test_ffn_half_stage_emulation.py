@@ -63,11 +63,24 @@ def test_half_stage_loads_cover_the_stage(gu):
                 assert (arr, row) == ("w2", expert * N_out + nt * 256 + lds_row)
 
 
+@pytest.mark.parametrize("rows", range(1, E.BM + 1, 3))
+def test_loaders_of_waves_with_rows_load_a(rows):
+    """A loader brings A rows if its own wave row w // 2 has rows (a_on): then every 64-row block that a computing wave
+    reads is loaded, and a tile of at most 64 rows has two loaders' A loads, not four."""
+    a_on = [w // E.WAVES_N * E.WM < rows for w in range(E.NL)]
+    for wm in range(E.BM // E.WM):
+        assert not wm * E.WM < rows or a_on[wm]
+    assert sum(a_on) == (2 if rows <= E.WM else 4)
+
+
+@pytest.mark.parametrize("loads_a", [True, False])
 @pytest.mark.parametrize("KT", [2, 4, 12, 22, 112])
-def test_half_stage_pipeline_order(KT):
+def test_half_stage_pipeline_order(KT, loads_a):
     """Program order of one tile over the parts A, Q0..Q3 of its stages; an epoch is the time between two
-    barriers, which all waves share."""
-    loads_of = {"A": E.ALD, "Q0": HALF_B // 2, "Q1": HALF_B // 2, "Q2": HALF_B // 2, "Q3": HALF_B // 2}
+    barriers, which all waves share.  loads_a: the loader brings A rows (its own wave has rows), or only B; its waits
+    count what it has in flight."""
+    a_ld = E.ALD if loads_a else 0
+    loads_of = {"A": a_ld, "Q0": HALF_B // 2, "Q1": HALF_B // 2, "Q2": HALF_B // 2, "Q3": HALF_B // 2}
     queue, landed = [], {}                # the loader's loads in order; landed[stage, part]: the epoch it is safe from
     reads, issues = [], []                # (epoch, stage, part)
     epoch = 0
@@ -98,13 +111,13 @@ def test_half_stage_pipeline_order(KT):
         read(kt, "A", "Q1")
         if next1:
             issue(kt + 1, "Q2", "Q3")
-        wait(E.ALD + 8 if next1 else 0)
+        wait(a_ld + 8 if next1 else 0)
         epoch += 1                                        # barrier a
         read(kt, "Q2", "Q3")
         if next2:
             issue(kt + 2, "A")
         if next1:
-            wait(E.ALD + 4 if next2 else 4)
+            wait(a_ld + 4 if next2 else 4)
         epoch += 1                                        # barrier c
         if next1:
             read(kt + 1, "Q0", "A")
