@@ -51,10 +51,9 @@ __device__ __forceinline__ void static_for(F&& f) {
 }
 
 // ------------------------------------------------------------------ tile scheduler
-// Fills mt_prefix[0..E_loc] (m-tiles before each expert) and row bounds.
-template <int BM>
-__device__ void build_schedule(const int32_t* row_offsets, int E_loc, int max_rows, int* mt_prefix,
-                               int* row_begin, int* row_end) {
+// Row bounds of every expert.
+__device__ __forceinline__ void expert_rows(const int32_t* row_offsets, int E_loc, int max_rows, int* row_begin,
+                                            int* row_end) {
     const int base = row_offsets[0];
     for (int l = threadIdx.x; l < E_loc; l += blockDim.x) {
         int b = row_offsets[l] - base, e = row_offsets[l + 1] - base;
@@ -62,8 +61,14 @@ __device__ void build_schedule(const int32_t* row_offsets, int E_loc, int max_ro
         e = max(b, min(e, max_rows));
         row_begin[l] = b;
         row_end[l] = e;
-        mt_prefix[l + 1] = (e - b + BM - 1) / BM;
     }
+}
+
+// Fills mt_prefix[0..E_loc] (m-tiles before each expert) from this thread's own
+// expert_rows; ends in a barrier.
+template <int BM>
+__device__ void build_schedule(int E_loc, int* mt_prefix, const int* row_begin, const int* row_end) {
+    for (int l = threadIdx.x; l < E_loc; l += blockDim.x) mt_prefix[l + 1] = (row_end[l] - row_begin[l] + BM - 1) / BM;
     if (threadIdx.x == 0) mt_prefix[0] = 0;
     __syncthreads();
     for (int off = 1; off < E_loc; off <<= 1) {
@@ -1392,25 +1397,35 @@ __global__ __launch_bounds__(kNW * kWave, 1) void ffn_fused_bf16_kernel(
 // tiles read each operand less often (RB = 4, CB = 2: 1,692 rows over 2 experts
 // of d = 328, inter = 717 127 us, 273 through the LDS tiles).
 // A4: K is a multiple of 4, so every row is 16-byte aligned.
-constexpr int kF32Waves = 4;                 // waves per workgroup, a tile each
+constexpr int kF32Waves = 4;                 // a wave a tile, in groups of four that share weight rows
+// Small tiles, in halves per CU, from which a GEMM takes the large ones, if
+// those hold three of the eight small tiles they have room for: up to four
+// large tiles per CU take the time of one, small ones a time that grows with
+// their number, and less of it for a short K (the loads of one batch cover K =
+// 128).  Measured, us (all small / gate/up large): 800 rows over 2 experts of d =
+// inter = 1024 (12.5 small tiles per CU) 164 / 145; 1,280 rows over 32 experts
+// of d = inter = 512 (12, three of four rows) 68 / 80; 1,400 rows over 2 experts
+// of d = 328, inter = 717 (15.5) 93 / 101; 4,000 rows over 2 experts of d = 128,
+// inter = 256 (15.6) 29 / 32.
+__host__ __device__ constexpr int f32_large_from(int K) { return K <= 128 ? 40 : K < 512 ? 32 : 25; }
+// Groups of a workgroup.  Where the rows settle the form on the device, a
+// workgroup has as many waves as its CU holds of that kernel and the launch one
+// per CU: few tiles then spread over all CUs (of two workgroups the dispatcher
+// may put both on one).
+constexpr int f32_groups(bool gateup, bool large) { return !large ? 1 : gateup ? 2 : 3; }
 
 template <bool GATEUP, int RB, int CB, bool A4>
-__global__ __launch_bounds__(kF32Waves * kWave) void ffn_gemm_f32_kernel(
-    const float* __restrict__ A, const float* __restrict__ B0, const float* __restrict__ B1,
-    float* __restrict__ C, const int32_t* __restrict__ row_offsets, int E_loc, int max_rows, int K, int N_out,
-    const int32_t* __restrict__ row_src, int x_rows) {
+__device__ __forceinline__ void f32_tiles(const float* __restrict__ A, const float* __restrict__ B0,
+                                          const float* __restrict__ B1, float* __restrict__ C, const int* mt_prefix,
+                                          const int* row_begin, const int* row_end, int E_loc, int K, int N_out,
+                                          const int32_t* __restrict__ row_src, int x_rows, int first, int step) {
     constexpr int U = RB == 1 ? 8 : 2;       // K steps of 16 per batch of loads
-    __shared__ int mt_prefix[kMaxExpertsLocal + 1];
-    __shared__ int row_begin[kMaxExpertsLocal];
-    __shared__ int row_end[kMaxExpertsLocal];
-    build_schedule<RB * 16>(row_offsets, E_loc, max_rows, mt_prefix, row_begin, row_end);
     const int MT = mt_prefix[E_loc];
     const int n_tiles = (N_out + CB * 16 - 1) / (CB * 16);
     const int lane = threadIdx.x % kWave;
     const int r16 = lane & 15, g = lane >> 4;
-    const int wave = static_cast<int>(__builtin_amdgcn_readfirstlane(threadIdx.x / kWave));
-    // m-tile fastest: a workgroup's waves share their weight rows
-    for (int tile = blockIdx.x * kF32Waves + wave; tile < MT * n_tiles; tile += gridDim.x * kF32Waves) {
+    // m-tile fastest: the waves of a group share their weight rows
+    for (int tile = first; tile < MT * n_tiles; tile += step) {
         const int nt = tile / MT, m_tile = tile - nt * MT;
         const int l = __builtin_amdgcn_readfirstlane(find_expert(mt_prefix, E_loc, m_tile));
         const int row0 = __builtin_amdgcn_readfirstlane(row_begin[l] + (m_tile - mt_prefix[l]) * (RB * 16));
@@ -1506,27 +1521,65 @@ __global__ __launch_bounds__(kF32Waves * kWave) void ffn_gemm_f32_kernel(
     }
 }
 
+// LARGE: the row capacity allows large tiles, and the experts' rows, which may
+// be far fewer, settle it here, for each GEMM by itself (32 rows over 8 experts
+// of d = 2048, inter = 1408 with a capacity of 2,048 rows: 261 us when the
+// capacity chose large tiles for both, 67 so).
+template <bool GATEUP, bool LARGE, bool A4>
+__global__ __launch_bounds__((f32_groups(GATEUP, LARGE) * kF32Waves * kWave)) void ffn_gemm_f32_kernel(
+    const float* __restrict__ A, const float* __restrict__ B0, const float* __restrict__ B1,
+    float* __restrict__ C, const int32_t* __restrict__ row_offsets, int E_loc, int max_rows, int K, int N_out,
+    const int32_t* __restrict__ row_src, int x_rows, int cus) {
+    __shared__ int mt_prefix[kMaxExpertsLocal + 1];
+    __shared__ int row_begin[kMaxExpertsLocal];
+    __shared__ int row_end[kMaxExpertsLocal];
+    const int wave = static_cast<int>(__builtin_amdgcn_readfirstlane(threadIdx.x / kWave));
+    const int first = (wave / kF32Waves * gridDim.x + blockIdx.x) * kF32Waves + wave % kF32Waves;
+    const int step = gridDim.x * f32_groups(GATEUP, LARGE) * kF32Waves;
+    expert_rows(row_offsets, E_loc, max_rows, row_begin, row_end);
+    build_schedule<16>(E_loc, mt_prefix, row_begin, row_end);
+    if constexpr (LARGE) {
+        const long long small = static_cast<long long>(mt_prefix[E_loc]) * ((N_out + 15) / 16);
+        if (2 * small >= static_cast<long long>(f32_large_from(K)) * cus) {
+            __syncthreads();
+            build_schedule<64>(E_loc, mt_prefix, row_begin, row_end);
+            const long long large = static_cast<long long>(mt_prefix[E_loc]) * ((N_out + 31) / 32);
+            if (small >= 3 * large) {
+                // gate/up: one wave per SIMD (two read more than the L1 keeps: 2,000
+                // rows of d = 2048, inter = 1408 505 us, 568 with two)
+                if (!GATEUP || wave < kF32Waves)
+                    f32_tiles<GATEUP, 4, 2, A4>(A, B0, B1, C, mt_prefix, row_begin, row_end, E_loc, K, N_out, row_src,
+                                                x_rows, first, GATEUP ? static_cast<int>(gridDim.x) * kF32Waves : step);
+                return;
+            }
+            __syncthreads();
+            build_schedule<16>(E_loc, mt_prefix, row_begin, row_end);
+        }
+    }
+    f32_tiles<GATEUP, 1, 1, A4>(A, B0, B1, C, mt_prefix, row_begin, row_end, E_loc, K, N_out, row_src, x_rows,
+                                first, step);
+}
+
 template <bool GATEUP>
 void launch_ffn_f32(const float* a, const float* b0, const float* b1, float* c, const int32_t* row_offsets, int E_loc,
                     int max_rows, int K, int N_out, const int32_t* row_src, int x_rows, hipStream_t st) {
-    // larger tiles from the row capacity on at which they give every SIMD a wave
     const long long cus = device_cu_count();
-    const long long large = (max_rows / 64 + E_loc) * static_cast<long long>((N_out + 31) / 32);
-    const long long small = (max_rows / 16 + E_loc) * static_cast<long long>((N_out + 15) / 16);
-    const bool big = large >= 4 * cus;
-    const long long need = ((big ? large : small) + kF32Waves - 1) / kF32Waves;
-    const int grid = static_cast<int>(need < 8 * cus ? need : 8 * cus);
-    const bool a4 = (K & 3) == 0;
-    auto go = [&](auto kernel) {
-        kernel<<<grid, kF32Waves * kWave, 0, st>>>(a, b0, b1, c, row_offsets, E_loc, max_rows, K, N_out, row_src, x_rows);
+    const long long small = (max_rows / 16 + E_loc) * static_cast<long long>((N_out + 15) / 16);   // most there can be
+    const long long need = (small + kF32Waves - 1) / kF32Waves;
+    auto by_form = [&](auto A4) {
+        auto go = [&](auto Large, long long most) {
+            constexpr bool large = decltype(Large)::value;
+            ffn_gemm_f32_kernel<GATEUP, large, decltype(A4)::value>
+                <<<static_cast<int>(need < most ? need : most), f32_groups(GATEUP, large) * kF32Waves * kWave, 0, st>>>(
+                    a, b0, b1, c, row_offsets, E_loc, max_rows, K, N_out, row_src, x_rows, static_cast<int>(cus));
+        };
+        if (2 * small >= f32_large_from(K) * cus) go(std::true_type{}, cus);
+        else go(std::false_type{}, 8 * cus);
     };
-    if (big) {
-        if (a4) go(ffn_gemm_f32_kernel<GATEUP, 4, 2, true>);
-        else go(ffn_gemm_f32_kernel<GATEUP, 4, 2, false>);
-    } else {
-        if (a4) go(ffn_gemm_f32_kernel<GATEUP, 1, 1, true>);
-        else go(ffn_gemm_f32_kernel<GATEUP, 1, 1, false>);
-    }
+    // the gate/up GEMM's K is d, a multiple of four
+    if constexpr (GATEUP) by_form(std::true_type{});
+    else if ((K & 3) == 0) by_form(std::true_type{});
+    else by_form(std::false_type{});
 }
 
 int persistent_grid(long long tiles_upper) {

@@ -4,6 +4,7 @@ import pytest
 import torch
 
 from paper_2607_05116_amd import capi
+from tests.ffn_forms import f32_large, f32_open
 
 pytestmark = pytest.mark.gpu
 
@@ -15,6 +16,10 @@ pytestmark = pytest.mark.gpu
     (132, 64, [3, 0, 130], 140),                   # K one step past a batch
     (64, 2048, [700, 0, 900], 2000),               # large tiles in the gate/up GEMM, small ones in the down GEMM
     (2048, 63, [1500, 1], 1600),                   # large tiles, K not a multiple of four, in the down GEMM
+    (256, 320, [9, 0, 3, 40], 4000),               # a capacity for large tiles, rows for small ones
+    (64, 512, [16] * 160, 3000),                   # many small tiles, but three quarters of every large one empty
+    (256, 768, [700, 33, 900], 1700),              # large tiles in the gate/up GEMM, remainders of 16 and of 64
+    (1024, 128, [700, 33, 900], 1700),             # the same in the down GEMM
 ])
 @pytest.mark.parametrize("gathered", [False, True])
 def test_ffn_f32_tiles(d, inter, counts, cap, gathered):
@@ -50,3 +55,34 @@ def test_ffn_f32_tiles(d, inter, counts, cap, gathered):
     assert float(err.norm() / ref.norm()) <= bound
     assert float(err.abs().max()) <= 6 * bound * float(ref.abs().max())
     assert not y[rows:].any()
+
+
+def test_ffn_f32_forms_of_the_cases():
+    """The capacity-bound cases above take the tiles their comments name, and their capacity leaves both open."""
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    for d, inter, counts, cap, gu, dn in ((256, 320, [9, 0, 3, 40], 4000, False, False),
+                                          (64, 512, [16] * 160, 3000, False, False),
+                                          (256, 768, [700, 33, 900], 1700, True, False),
+                                          (1024, 128, [700, 33, 900], 1700, False, True),
+                                          (64, 2048, [700, 0, 900], 2000, True, False),
+                                          (2048, 63, [1500, 1], 1600, False, True)):
+        assert f32_large(counts, d, inter, cus) == gu and f32_large(counts, inter, d, cus) == dn, (d, inter)
+        assert f32_open(cap, len(counts), d, inter, cus) or f32_open(cap, len(counts), inter, d, cus)
+
+
+def test_ffn_f32_capacity_gives_the_same_bits():
+    """The tiles follow the rows: a capacity many times the rows changes nothing."""
+    d, inter, counts = 512, 512, [4, 60, 0, 17]
+    g = torch.Generator(device="cuda").manual_seed(8)
+    w = [torch.randn(s, generator=g, device="cuda") * 0.05 for s in ((4, inter, d), (4, inter, d), (4, d, inter))]
+    offs = torch.tensor(np.concatenate([[0], np.cumsum(counts)]), dtype=torch.int32, device="cuda")
+    rows, outs = sum(counts), []
+    x = torch.randn((8000, d), generator=g, device="cuda")
+    for cap in (rows, 8000):
+        y = torch.zeros((cap, d), device="cuda")
+        ws = torch.empty(capi.cap_workspace_size(capi.CAP_OP_EXPERT_FFN, None, d, inter, cap, capi.CAP_DTYPE_F32),
+                         dtype=torch.uint8, device="cuda")
+        capi.cap_expert_ffn(capi.CAP_DTYPE_F32, 4, d, inter, cap, x[:cap], offs, *w, y, ws)
+        outs.append(y[:rows])
+    torch.cuda.synchronize()
+    assert torch.equal(outs[0].view(torch.int32), outs[1].view(torch.int32))
