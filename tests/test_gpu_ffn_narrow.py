@@ -7,6 +7,7 @@ import torch
 import oracle
 from paper_2607_05116_amd import capi
 from tests import cases as C
+from tests.ffn_forms import bf16_form, bf16_tiles
 from workloads import generator as gen
 
 pytestmark = pytest.mark.gpu
@@ -35,14 +36,26 @@ def _f32(t):
     return t.float().cpu().numpy()
 
 
-@pytest.mark.parametrize("d,inter,counts,cap", [
-    (256, 128, [1], 1),                                  # two K stages in the down GEMM, one row
-    (512, 384, [15, 16, 17, 0, 31, 33], 200),
-    (1024, 256, [63, 64, 65, 0, 2, 129], 8192),          # the first launch of a call of the fused kernel's capacity
-    (512, 256, [1] * 70 + [0] * 30, 70),                 # more tiles than workgroups in turn
+def _cus():
+    return torch.cuda.get_device_properties(0).multi_processor_count
+
+
+EDGES = [1, 65, 127, 128, 129, 0]
+
+
+@pytest.mark.parametrize("d,inter,counts,cap,form", [
+    (256, 128, [1], 1, 64),                              # two K stages in the down GEMM, one row
+    (512, 384, [15, 16, 17, 0, 31, 33], 200, 64),
+    (1024, 256, [63, 64, 65, 0, 2, 129], 8192, 64),      # the first launch of a call of the fused kernel's capacity
+    (512, 256, [1] * 70 + [0] * 30, 70, 256),            # the forms cost the same: wide, a tile a workgroup
+    (256, 384, [40] * 200 + [0], 8000, 64),              # tiles in turn, in both GEMMs
+    (1024, 256, EDGES + [70] * 18, 1800, 128),           # 128-row tiles, a tile a workgroup in the gate/up GEMM
+    (1024, 256, EDGES + [100] * 66, 7100, 128),          # and in turn in both, the row counts at the tiles' edges
+    (1024, 256, EDGES + [100] * 66, 8300, 128),
 ])
 @pytest.mark.parametrize("gathered", [False, True])
-def test_narrow_ffn_against_oracle(d, inter, counts, cap, gathered):
+def test_narrow_ffn_against_oracle(d, inter, counts, cap, form, gathered):
+    assert bf16_form(counts, d, inter, _cus()) == form
     g = torch.Generator(device="cuda").manual_seed(len(counts) + d)
     E_loc, rows = len(counts), sum(counts)
     w = _weights(g, E_loc, d, inter)
@@ -64,6 +77,36 @@ def test_narrow_ffn_against_oracle(d, inter, counts, cap, gathered):
     assert ok, worst
     assert C.rel_fro(got, ref) <= 1e-2
     assert not y[rows:].any()
+
+
+@pytest.mark.parametrize("d,inter,counts,form", [(256, 384, [40] * 200 + [0], 64),
+                                                 (1024, 256, EDGES + [100] * 66, 128)])
+@pytest.mark.parametrize("cap", [8000, 9000])
+def test_narrow_tiles_in_turn_equal_wide_bits(d, inter, counts, form, cap):
+    """Calls of more narrow tiles than workgroups in both GEMMs (the ring of stages runs on across a workgroup's tiles)
+    give the wide tiles' bits: plain, gathered and with the destination combine.  A cap on the workgroups keeps a call
+    on wide tiles."""
+    n_cu, rows = _cus(), sum(counts)
+    assert bf16_form(counts, d, inter, n_cu) == form and min(bf16_tiles(counts, form, d, inter)) > n_cu
+    g = torch.Generator(device="cuda").manual_seed(form)
+    E_loc, w, offs = len(counts), _weights(g, len(counts), d, inter), _offs(counts)
+    x, ws = _bf(g, cap, d), _ws(d, inter, cap)
+    src = torch.randint(0, cap, (cap,), generator=g, device="cuda", dtype=torch.int32)
+    dst = torch.full((cap,), -1, dtype=torch.int32, device="cuda")
+    dst[:rows:2] = torch.randperm(cap, generator=g, device="cuda")[:len(dst[:rows:2])].to(torch.int32)
+    gate = torch.rand(cap, generator=g, device="cuda")
+    outs = []
+    for opt in (None, capi.make_ffn_options(max_workgroups=n_cu)):
+        y = [torch.zeros((cap, d), dtype=torch.bfloat16, device="cuda") for _ in range(4)]
+        capi.cap_expert_ffn_ex(CDT, E_loc, d, inter, cap, x, 0, None, offs, *w, y[0], ws, options=opt)
+        capi.cap_expert_ffn_ex(CDT, E_loc, d, inter, cap, x, cap, src, offs, *w, y[1], ws, options=opt)
+        capi.cap_expert_ffn_combine(CDT, E_loc, d, inter, cap, x, cap, src, offs, *w, y[2], dst, gate, y[3], cap, ws,
+                                    options=opt)
+        torch.cuda.synchronize()
+        outs.append(y)
+    for a, b in zip(*outs):
+        assert torch.equal(a.view(torch.int16), b.view(torch.int16))
+    assert all(t.any() for t in outs[0])
 
 
 @pytest.mark.parametrize("cap", [2600, 8300])

@@ -24,6 +24,7 @@ from paper_2607_05116_amd import capi  # noqa: E402
 from paper_2607_05116_amd.layer import DeviceLayer  # noqa: E402
 
 import oracle  # noqa: E402
+from tests.ffn_forms import bf16_form  # noqa: E402
 
 
 def _layer(case: C.Case, x=None, **kw) -> DeviceLayer:
@@ -668,13 +669,17 @@ def test_ffn_bf16_ragged_experts(counts):
 @pytest.mark.parametrize("d,inter,counts", [
     (256, 128, [3000, 0, 1, 257, 4100, 0, 900, 2000]),   # down GEMM of two K stages
     (512, 256, [9000]),                                   # every m-tile on one expert
-    (256, 384, [40] * 200 + [0] * 56),                    # 256 experts, one partial m-tile each
-    (256, 128, [100, 0, 200]),                            # two m-tiles: most XCD queues empty
+    (256, 384, [40] * 200 + [0] * 56),                    # 256 experts (narrow tiles)
+    (256, 128, [100, 0, 200]),                            # narrow tiles
+    (256, 384, [600] + [40] * 200 + [0] * 55),            # wide: 256 experts, most with one partial m-tile
+    (256, 128, [600, 0, 200]),                            # wide: four m-tiles, half of the XCD queues empty
     (512, 384, []),                                       # no rows at all
 ])
 def test_ffn_fused_ragged_experts(d, inter, counts):
     counts = counts or [0, 0, 0]
     rows = int(sum(counts))
+    if max(counts) > 512:
+        assert bf16_form(counts, d, inter, torch.cuda.get_device_properties(0).multi_processor_count) == 256
     got, ref = _ffn_direct("bf16", len(counts), d, inter, counts, seed=len(counts) + d,
                            max_rows=max(FUSED_MIN_ROWS, rows + 5))
     if rows == 0:
