@@ -237,3 +237,13 @@ def test_route_layout_validation(capi):
     bad = _topo(capi, k=0)
     assert f(ctypes.byref(bad), 0x3000, 0.3, 0x4000, 0x5000, 0x6000, 0x7000, ctypes.byref(lay), None, 0x10000,
              need, None) == capi.CAP_ERR_INVALID_ARG
+
+
+def test_smoke_ffn_runs_the_fused_kernel():
+    """smoke()'s bf16 FFN takes wide tiles with a row capacity of the fused kernel, the path the bench times."""
+    import __graft_entry__ as entry
+    from tests.ffn_forms import bf16_form
+    f = entry.SMOKE_FFN
+    assert f["max_rows"] >= 32 * 256 and sum(f["counts"]) <= f["max_rows"]
+    assert bf16_form(f["counts"], f["d"], f["inter"], 256) == 256
+    assert bf16_form([100, 0, 200], f["d"], f["inter"], 256) == 64      # few rows an expert would not
