@@ -556,12 +556,17 @@ def test_ffn_gather_equals_ffn_on_gathered_rows(name, kind, p):
 
 
 @pytest.mark.parametrize("dtype,d,inter,counts", [("bf16", 512, 384, [300, 1, 0, 513]),
+                                                  ("bf16", 512, 384, [30, 1, 0, 67]),       # narrow tiles of 64 rows
+                                                  ("bf16", 1024, 256, [129, 0, 1] + [100] * 66),  # and of 128
                                                   ("bf16", 256, 128, [0, 700, 40]),
                                                   ("bf16", 256, 128, [3000, 1, 0, 5200]),  # fused kernel
                                                   ("f32", 128, 256, [70, 0, 131])])
 def test_ffn_gather_ragged_with_repeats_and_clamping(dtype, d, inter, counts):
     """Ragged experts, repeated source rows and out-of-range indices (clamped
     into [0, x_rows)) against cap_expert_ffn on the explicitly gathered rows."""
+    if dtype == "bf16":
+        form = bf16_form(counts, d, inter, torch.cuda.get_device_properties(0).multi_processor_count)
+        assert form == (256 if max(counts) > 512 else 128 if len(counts) > 9 else 64)
     rng = np.random.default_rng(len(counts) + d)
     E_loc, rows = len(counts), int(sum(counts))
     offs = torch.from_numpy(np.concatenate([[0], np.cumsum(counts)]).astype(np.int32) + 9).cuda()
