@@ -291,14 +291,17 @@ __device__ __forceinline__ void load_half1(Loads& s, uint32_t b_lds, int buf) {
 // last LDS read of the tile (barrier c of the last stage), and buffer 0 was
 // free from barrier a of the last stage (the hook may issue the next tile's
 // stage 0).
-// What bounds it: the board's power at 1.8 GHz (MFMA pipes 72 % busy on the
-// 33,234 rows of d = 7168, inter = 2048, where loading each stage whole behind
-// one barrier kept them 63 % busy), then the LDS, whose fragment reads and
-// direct writes need 256 KB a stage, the time of its MFMAs at 128 bytes a
-// clock.  That call 2328 -> 2131 us, 44,420 rows of d = 2048, inter = 768
-// 393 -> 358 us, 3,001 rows of d = 2048, inter = 1408 98 -> 89 us.  Issuing
-// twelve of a stage's sixteen loads in quarters 1 and 2 was no faster, nor a
-// raised wave priority around the MFMAs or for the loaders (0 to 2 % slower).
+// What bounds it: the board's power (under the counters the MFMA pipes are 73 %
+// busy at 1.7 GHz on the 33,234 rows of d = 7168, inter = 2048, where loading
+// each stage whole behind one barrier kept them 62 % busy at 1.8 GHz), then the
+// LDS, whose fragment reads and direct writes need 256 KB a stage, the time of
+// its MFMAs at 128 bytes a clock; on tiles of few stages (a down tile of inter =
+// 768 has twelve) also the next tile's stage 1, which cannot be issued before
+// the epilogue has given its buffer back.  That call 2328 -> 2131 us, 44,420
+// rows of d = 2048, inter = 768 393 -> 358 us, 3,001 rows of d = 2048, inter =
+// 1408 98 -> 89 us.  Issuing twelve of a stage's sixteen loads in quarters 1 and
+// 2 was no faster, nor a raised wave priority around the MFMAs or for the
+// loaders (0 to 2 % slower).
 // A wave whose 64 rows all lie past the tile's valid rows (active = false)
 // computes nothing: its accumulators stay zero and are never stored.  A loader
 // among them loads no A either, and its waits count without those loads: tiles
@@ -1010,10 +1013,10 @@ __global__ __launch_bounds__(kNW * kWave, 1) void ffn_gemm_bf16_kernel(
     const uint32_t lds_base = static_cast<uint32_t>(reinterpret_cast<uintptr_t>((lds_void*)lds));
     const uint32_t a_lds = lds_base + wave * kALd * 1024;             // loader waves' parts of a stage
     const uint32_t b_lds = lds_base + (kBM + (wave >> 1) * kWN + (wave & 1) * 16) * kRowB;
-    // combine plan of a down tile: each storer lane loads one row's entry at
-    // the third stage (after the second, where the fused kernel's storers
+    // combine plan of a down tile: each storer lane loads one row's entry in
+    // the last stage but one (after the stage where the fused kernel's storers
     // wait for their previous stores to drain) and writes it to the LDS table
-    // at the last; the epilogue reads the table after the K loop's final
+    // in the last; the epilogue reads the table after the K loop's final
     // barrier
     const bool comb = !GATEUP && cp.dst != nullptr;
     int pl_d = -1;
@@ -1608,8 +1611,8 @@ size_t ffn_workspace_bytes(int max_rows, int inter, cap_dtype dt) {
     return ffn_h_bytes(max_rows, inter, dt) + (dt == CAP_DTYPE_BF16 ? sizeof(int) * fused_sync_ints(max_rows) : 0);
 }
 
-// bf16: the direct loads form 8-row block offsets (16 K bytes) with 24-bit
-// multiplies, so K = d or inter stays below 2^20 (2^19 here).
+// bf16: d and inter up to 2^19, so that a tile's 256 rows of K = d or inter
+// (2^28 bytes) stay far inside the direct loads' 32-bit lane offsets.
 cap_status ffn_supported(cap_dtype dt, int d, int inter) {
     if (dt == CAP_DTYPE_BF16)
         return (d % kBN == 0 && inter % (kBN / 2) == 0 && d <= (1 << 19) && inter <= (1 << 19)) ? CAP_OK

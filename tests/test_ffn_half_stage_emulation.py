@@ -1,8 +1,9 @@
-"""CPU emulation of the bf16 expert FFN's half-stage pipeline (k_loop and
-issue_half of expert_ffn.hip).
+"""CPU emulation of the bf16 expert FFN's stage pipeline (k_loop, load_half0
+and load_half1 of expert_ffn.hip).
 
-A stage (K = 64 of a 256 x 256 tile) is loaded in two halves, each issued as
-soon as the part of LDS it overwrites has been read by every wave.  The test
+A stage (K = 64 of a 256 x 256 tile) is loaded in parts (A, and the four
+quarters of B, two of them a half), each issued as soon as the LDS space it
+overwrites has been read by every wave.  The test
 replays the program order of the loader and compute waves on the host:
 
 * the loader waves' direct loads cover every 8-row block of a stage once, with
@@ -27,7 +28,7 @@ def b_loads(half, lw):
 
 
 def b_source_row(gu, lw, half, q, i, nt, expert, N_out):
-    """(array, row) that tile_src and issue_half address for that block's first row."""
+    """(array, row) that tile_loads and load_b address for that block's first row."""
     wn, h = lw >> 1, lw & 1
     if gu:
         row = expert * N_out + nt * (E.BN // 2) + wn * (E.WN // 2) + h * 16
@@ -47,7 +48,7 @@ def test_half_stage_loads_cover_the_stage(gu):
                 for lds_row, q, i in b_loads(half, lw):
                     arr, row = b_source_row(gu, lw, half, q, i, nt, expert, N_out)
                     assert lds_row % 8 == 0 and 0 <= lds_row < E.BN and lds_row not in seen
-                    # the swizzle of the block's rows depends on the block's parity: lane_off[i & 1]
+                    # the swizzle of the block's rows depends on the block's parity: col_b[i & 1] of lane_map
                     assert (lds_row // 8) % 2 == i % 2
                     # the half holds exactly the wave columns' quarters 2 half, 2 half + 1
                     assert (lds_row % E.WN) // 64 == half

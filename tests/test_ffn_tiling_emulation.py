@@ -14,9 +14,8 @@ checks it on the host:
 * the two-kernel path's block -> worker map is a permutation;
 * for every tile of both GEMMs, the first and last K stage of every direct load
   of every loader wave and lane: the global byte offset stays inside its
-  operand (x or the expert-sorted rows, W1 / W3 / W2, H), fits in 32 bits, the
-  24-bit multiplies stay below 2^24, and the LDS destination stays inside the
-  two stage buffers;
+  operand (x or the expert-sorted rows, W1 / W3 / W2, H), the per-lane offset
+  fits in 32 bits, and the LDS destination stays inside the two stage buffers;
 * the epilogue's output rows and 8-column chunks stay inside H / Y.
 
 Shapes: rank 0 and the last rank of the Qwen3-, DeepSeek-V2-Lite- and
@@ -25,6 +24,8 @@ experts, ragged synthetic experts (empty experts, one-row experts, capacity
 cuts) and gathered rows at the 4 GiB limit of x.
 """
 from __future__ import annotations
+
+import itertools
 
 import numpy as np
 import pytest
@@ -40,7 +41,6 @@ ROWS_PER_LOAD = 1024 // ROW_B
 NW, NL = 8, 4
 ALD = BM // ROWS_PER_LOAD // NL
 BLD = BN // ROWS_PER_LOAD // NL
-BRUN = BLD // 2
 STAGE_BYTES = (BM + BN) * ROW_B
 STAGES = 2
 WAVES_N = 2
@@ -112,7 +112,7 @@ def check_loads(gu, l, row0, rows, nt, K, N_rows_b, a_rows_cap, gathered, row_sr
     """Every direct load of the tiles (vectors over tiles) at stages 0 and KT-1."""
     pitch = K * 2
     blk = ROWS_PER_LOAD * pitch
-    assert blk < (1 << 24) and pitch < (1 << 24)
+    assert BM * pitch < (1 << 32)
     KT = K // STAGE_K
     for kt in (0, KT - 1):
         kb = kt * STAGE_K * 2
@@ -138,19 +138,20 @@ def check_loads(gu, l, row0, rows, nt, K, N_rows_b, a_rows_cap, gathered, row_sr
                     assert (i * blk + LD_ROW.max() * pitch + cb.max()) < (1 << 32)
                 lds = (kt % STAGES) * STAGE_BYTES + lw * ALD * 1024 + i * 1024
                 assert 0 <= lds and lds + 1024 <= STAGES * STAGE_BYTES
-            for i in range(BLD):
-                cb = COL_B[(lw * BLD + i) & 1]
-                if gu:
-                    first = l * inter + nt * (BN // 2) + lw * 32          # W1 and W3 runs
-                    brow = first[:, None] + (i % BRUN) * ROWS_PER_LOAD + LD_ROW[None, :]
+            # B quarter 2 half + q of wave column wn, 16 rows h: two 8-row blocks
+            wn, h = lw >> 1, lw & 1
+            for half, q, i in itertools.product(range(2), range(2), range(2)):
+                if gu:                                                    # W1 (q = 0) and W3
+                    first = l * inter + nt * (BN // 2) + wn * (WN // 2) + h * 16 + half * 32
                 else:
-                    first = l * d + nt * BN + lw * BLD * ROWS_PER_LOAD + (i // BRUN) * 32
-                    brow = first[:, None] + (i % BRUN) * ROWS_PER_LOAD + LD_ROW[None, :]
-                off = brow * pitch + cb[None, :] + kb
+                    first = l * d + nt * BN + wn * WN + h * 16 + half * 64 + q * 32
+                brow = first[:, None] + i * ROWS_PER_LOAD + LD_ROW[None, :]
+                off = brow * pitch + COL_B[i][None, :] + kb
                 assert brow.min() >= 0 and brow.max() < N_rows_b
                 assert off.max() + 16 <= N_rows_b * pitch
-                lds = (kt % STAGES) * STAGE_BYTES + BM * ROW_B + lw * BLD * 1024 + i * 1024
-                assert lds + 1024 <= STAGES * STAGE_BYTES
+                lds_row = wn * WN + h * 16 + half * 64 + q * 32 + i * ROWS_PER_LOAD
+                lds = (kt % STAGES) * STAGE_BYTES + (BM + lds_row) * ROW_B
+                assert lds + 1024 <= (kt % STAGES + 1) * STAGE_BYTES
 
 
 def check_stores(gu, row0, rows, nt, N_out, out_rows_cap):
